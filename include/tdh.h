@@ -82,22 +82,23 @@ typedef struct {
   double bh_x0[3], v_frame[3]; /* point-mass position at t = 0 and frame velocity */
   int inv_mode;   /* table inversion (every mode gives the same cell, hence the same result):
                      0 bisection for every query;
-                     2 before each stage a pass bisects for the table cell of every
-                       cell's stage-input state; that cell seeds the cell's face and
-                       compression queries (a face's right state is seeded by its
-                       left state's cell);
-                     1 as 2, but each stage records the table cells of its output
-                       states for the next stage instead of a pass, their searches
+                     1 each stage's face and compression queries start from the table
+                       cell of the cell's stage-input state (a face state from its
+                       own cell's) and step to their own; each stage records the
+                       table cells of its output states for the next, their searches
                        starting from the learned network's prediction (tdh_mlp_*;
-                       from the input state's cell while the network is off);
-                     3 as 1 with every search starting from the input state's cell;
-                     4 as 2 with the pass's searches starting from the learned
-                       network's prediction (bisection while the network is off).
-                     In modes 1 and 3 a pass finds the cells once after a state
-                     upload (with the network in mode 1).  In modes 2 and 4 the
-                     CFL reduction (tdh_reduce_dt) records the cells of the state
-                     it reduces over (its search for c_s finds them), and the
-                     next window's first stage runs without a pass. */
+                       while the network is off as in mode 3);
+                     3 as 1 with every search starting from the cell of the nearest
+                       query at hand;
+                     2 as 3;
+                     4 as 3 with the searches of cells for which none is held
+                       starting from the learned network's prediction (bisection
+                       while the network is off).
+                     Where no cells are held (after a state upload) a pass before the
+                     first stage finds them: with the network in modes 1 and 4, by
+                     bisection in modes 2 and 3.  In modes 2 and 4 the CFL reduction
+                     (tdh_reduce_dt) records the cells of the state it reduces over
+                     (its search for c_s finds them), and no pass is needed. */
   int newton_max_iter; /* seeded secant steps before falling back to bisection (>= 0) */
   int riemann;    /* 0 HLLC (Toro Sec. 10.4); 1 HLLE, the solver of the paper's production
                      runs (Table 1): the HLL flux with the same Davis wave-speed bounds */

@@ -44,8 +44,7 @@ struct tdh_ctx {
   int *jc = nullptr;  // seed table cells: a segment of ncells per state buffer (Qa, Qb, Qs)
   double *flx = nullptr;  // face fluxes of the split stage form (3 axes)
   long long ftotal = 0;   // faces of one axis over all blocks
-  bool seeds_held = false;  // the current buffers' segments hold the cells of the current state
-  bool cfl_seeds = false;   // modes 2, 4: the CFL pass recorded them and no stage has run since
+  bool seeds_held = false;  // the current buffers' segments hold seeds of the current state
   bool cfl_parts = false;   // the last window's second stages left every tile's CFL minimum of this state
   BlockInfo *d_blocks = nullptr;
   int *d_lmap = nullptr, *d_fac = nullptr, *d_par = nullptr, *d_order = nullptr, *d_item_start = nullptr;
@@ -541,7 +540,6 @@ extern "C" tdh_status tdh_init_blocks(tdh_ctx *c, const tdh_mesh *m, void *dev_a
   HIPCHK(c, hipMemcpyAsync(c->Qa, host_state, L.total * sizeof(double), hipMemcpyHostToDevice, c->stream));
   if (c->jc) HIPCHK(c, hipMemsetAsync(c->jc, 0xff, 3 * L.ncells * sizeof(int), c->stream));  // no seeds yet (-1)
   c->seeds_held = false;
-  c->cfl_seeds = false;
   c->cfl_parts = false;
   if (c->phi) HIPCHK(c, hipMemcpyAsync(c->phi, host_phi, L.ptotal * sizeof(double), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -645,7 +643,6 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   c->tab.ex = c->d_table + fn_off + 256;
   c->have_table = true;
   c->seeds_held = false;  // cells of another table
-  c->cfl_seeds = false;
   c->cfl_parts = false;
   for (auto &g : c->graphs) hipGraphExecDestroy(g.second);
   c->graphs.clear();
@@ -718,7 +715,7 @@ static tdh_status reduce_dt_impl(tdh_ctx *c, double *part, double *dtb_dev, bool
     HIPCHK(c, launch_cfl(a, c->cfg.cfl, c->t, c->d_cfl_item_block, c->cfl_nitems, part, c->nb,
                          c->d_cfl_block_start, dtb_dev, c->cus, c->stream));
     c->stats.kernel_launches += 2;
-    c->cfl_seeds = c->cfg.eos_kind == 1 && (c->cfg.inv_mode == 2 || c->cfg.inv_mode == 4);
+    if (c->cfg.eos_kind == 1 && (c->cfg.inv_mode == 2 || c->cfg.inv_mode == 4)) c->seeds_held = true;
   }
   HIPCHK(c, hipMemcpyAsync(c->h_dtb.data(), dtb_dev, c->nb * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -803,10 +800,6 @@ static tdh_status collect_timing(tdh_ctx *c) {
 static tdh_status timed_stage(tdh_ctx *c, const StageArgs &a) {
   const bool t = c->timing && !c->capturing;
   tdh_status s;
-  if (c->cfg.eos_kind == 1 && (c->cfg.inv_mode == 2 || c->cfg.inv_mode == 4) && !(a.k == 0 && a.phase == 1)) {
-    HIPCHK(c, launch_seed(a, c->cus, c->stream));
-    c->stats.kernel_launches++;
-  }
   if (t && 2 * (c->ev_used + 1) > c->ev.size())
     if ((s = collect_timing(c))) return s;
   if (t) HIPCHK(c, hipEventRecord(c->ev[2 * c->ev_used], c->stream));
@@ -819,20 +812,16 @@ static tdh_status timed_stage(tdh_ctx *c, const StageArgs &a) {
   return TDH_OK;
 }
 
-// Seeds of a window's first stage.  Modes 1 and 3 carry seed cells from stage
-// to stage; after a state upload a pass over every block finds them once.
-// Modes 2 and 4 take them from the CFL pass when it ran on this state, else
-// from a pass over every block here.  Outside any captured graph, so a
-// window's graph never holds its first seed pass.
+// Seeds of a window's first stage.  Every stage records the table cells of its
+// output states, and in modes 2 and 4 the CFL pass those of the state it reads;
+// only where neither has run since the state was set (an upload, a remap, a
+// boost, another table) a pass over every block finds them here, outside any
+// captured graph.  In the stage the search costs a record look-up more per cell;
+// a pass of its own before each stage took 80 of 700 us of the 128^3 table-EOS
+// step and 9 to 13 % of the production-shaped windows.
 static tdh_status ensure_seeds(tdh_ctx *c) {
-  if (c->cfg.eos_kind != 1) return TDH_OK;
-  const bool carried = c->cfg.inv_mode == 1 || c->cfg.inv_mode == 3;
-  const bool per_stage = c->cfg.inv_mode == 2 || c->cfg.inv_mode == 4;
   c->cfl_parts = false;  // this window's second stages overwrite them
-  if (!(carried && !c->seeds_held) && !(per_stage && !c->cfl_seeds)) {
-    c->cfl_seeds = false;  // consumed by this window
-    return TDH_OK;
-  }
+  if (c->cfg.eos_kind != 1 || c->cfg.inv_mode == 0 || c->seeds_held) return TDH_OK;
   StageArgs a = base_args(c);
   a.k = 0;
   a.phase = 1;
@@ -840,9 +829,7 @@ static tdh_status ensure_seeds(tdh_ctx *c) {
   a.Lhi = kCntSlots - 2;
   HIPCHK(c, launch_seed(a, c->cus, c->stream));
   c->stats.kernel_launches++;
-  if (carried) c->seeds_held = true;
-  c->cfl_seeds = false;
-  c->cfl_parts = false;
+  c->seeds_held = true;
   return TDH_OK;
 }
 
@@ -893,10 +880,9 @@ static void account_subcycle(tdh_ctx *c, int k) {
 }
 
 static void finish_window(tdh_ctx *c) {
-  // a fused-form window leaves the CFL minima of its output state and, in modes
-  // 2 and 4, that state's table cells (every block's last second stage is in it)
+  // a fused-form window leaves the CFL minima of its output state (every
+  // block's last second stage is in it)
   c->cfl_parts = stage_cfl(c) && tile_is_fused(c->tile);
-  c->cfl_seeds = c->cfl_parts && c->cfg.eos_kind == 1 && (c->cfg.inv_mode == 2 || c->cfg.inv_mode == 4);
   c->t = c->t + c->dt_coarse;
   c->k = 0;
   c->stats.windows++;
@@ -1191,7 +1177,6 @@ extern "C" tdh_status tdh_remap(tdh_ctx *dst, tdh_ctx *src) {
                            dst->stream));
   if (dst->jc) HIPCHK(dst, hipMemsetAsync(dst->jc, 0xff, 3 * dst->ncells * sizeof(int), dst->stream));
   dst->seeds_held = false;
-  dst->cfl_seeds = false;
   dst->cfl_parts = false;
   dst->par.assign(dst->nb, 0);
   HIPCHK(dst, hipMemcpyAsync(dst->d_par, dst->par.data(), dst->nb * sizeof(int), hipMemcpyHostToDevice, dst->stream));
@@ -1211,7 +1196,6 @@ extern "C" tdh_status tdh_galilean_boost(tdh_ctx *c, const double *host_V, doubl
   HIPCHK(c, launch_boost(a.m, c->d_par, c->Qa, c->Qb, c->nv, host_V, rho_skip, c->stream));
   if (c->jc) HIPCHK(c, hipMemsetAsync(c->jc, 0xff, 3 * c->ncells * sizeof(int), c->stream));  // energies moved
   c->seeds_held = false;
-  c->cfl_seeds = false;
   c->cfl_parts = false;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return TDH_OK;
@@ -1251,7 +1235,6 @@ extern "C" tdh_status tdh_set_state(tdh_ctx *c, const double *host) {
   HIPCHK(c, hipMemcpyAsync(c->Qa, host, c->total * sizeof(double), hipMemcpyHostToDevice, c->stream));
   if (c->jc) HIPCHK(c, hipMemsetAsync(c->jc, 0xff, 3 * c->ncells * sizeof(int), c->stream));  // stale seeds go
   c->seeds_held = false;
-  c->cfl_seeds = false;
   c->cfl_parts = false;
   c->par.assign(c->nb, 0);
   HIPCHK(c, hipMemcpyAsync(c->d_par, c->par.data(), c->nb * sizeof(int), hipMemcpyHostToDevice, c->stream));
@@ -1495,10 +1478,8 @@ extern "C" tdh_status tdh_mlp_adam_step(tdh_ctx *c, const float *host_grad, floa
   HIPCHK(c, hipMemcpyAsync(c->d_mgrad, host_grad, kMlpParams * sizeof(float), hipMemcpyHostToDevice, c->stream));
   const int t = ++c->mlp_steps_done;
   const float c1 = (float)(1.0 - std::pow((double)b1, t)), c2 = (float)(1.0 - std::pow((double)b2, t));
-  HIPCHK(c, mlp_launch_adam(c->d_mw, c->d_mm, c->d_mv, c->d_mgrad, lr, b1, b2, eps, c1, c2, c->stream));
-  MlpDev &w = c->seed.w;
-  HIPCHK(c, mlp_launch_pack(c->d_mw, (short *)w.w1b, (short *)w.w2b, (short *)w.w2tb, (short *)w.w3b, (float *)w.b1,
-                            (float *)w.b2, (float *)w.b3, c->stream));
+  HIPCHK(c, mlp_launch_adam(c->d_mgrad, 1, nullptr, nullptr, 1, c->d_mw, c->d_mm, c->d_mv, lr, b1, b2, eps, c1, c2,
+                            c->seed.w, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   invalidate_graphs(c);
   return TDH_OK;
@@ -1511,7 +1492,9 @@ extern "C" tdh_status tdh_mlp_loss_grad(tdh_ctx *c, const double *dev_in, const 
   if (!dev_in || !dev_lT || n < 64 || n % 64 || n > kMlpMaxBatch)
     return fail(c, TDH_EINVAL, "n must be a multiple of 64 up to 65536");
   HIPCHK(c, mlp_launch_fwd_bwd(c->seed.w, c->seed, dev_in, dev_lT, n, (int)n, 0, 0, 0, c->d_mpart, c->d_mloss_part,
-                               c->d_mgrad, c->d_mloss, c->stream));
+                               c->stream));
+  HIPCHK(c, mlp_launch_reduce(c->d_mpart, (int)n / 64, c->d_mgrad, c->d_mloss_part, c->d_mloss, (int)n, c->seed.w,
+                              c->stream));
   if (host_grad)
     HIPCHK(c, hipMemcpyAsync(host_grad, c->d_mgrad, kMlpParams * sizeof(float), hipMemcpyDeviceToHost, c->stream));
   if (host_loss) HIPCHK(c, hipMemcpyAsync(host_loss, c->d_mloss, sizeof(float), hipMemcpyDeviceToHost, c->stream));

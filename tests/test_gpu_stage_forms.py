@@ -1,0 +1,106 @@
+"""The stage kernel's tile shapes on meshes where a tile's surface is most of
+its faces: blocks of eight cells that are their own periodic neighbours,
+outflow edges, unequal cell widths and both Riemann solvers.  Every fused shape
+gives the split form's bits, and both stay within the parity bar of the
+oracle, whose update is written cell by cell."""
+import numpy as np
+import pytest
+
+from paper_2609_37859_amd import workloads as W
+from tests.parity import TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tdh():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_37859_amd import tdh as T
+    T.lib()
+    return T
+
+
+def _case(name, table):
+    if name == "one_block":  # a single 8^3 block, periodic on itself
+        cfg = W.Config()
+        mesh = W.uniform_mesh(1, 1, 1, 8, (0.125, 0.1, 0.15))
+    elif name == "row_outflow_hlle":  # outflow edges at every block, dual energy, HLLE
+        cfg = W.Config(dual=1, riemann=1)
+        mesh = W.uniform_mesh(3, 1, 2, 8, 0.05, bc=(1, 1, 0))
+    elif name == "mixed_edges":  # 8^3 beside 16^3 blocks
+        cfg = W.Config(dual=1)
+        split = np.zeros((1, 2, 2), dtype=bool)
+        split[0, 1, 0] = True
+        mesh = W.mixed_mesh((2, 2, 1), 16, split, 0.03, bc=(1, 0, 1))
+    else:  # the table EOS, seeded
+        cfg = W.Config(eos_kind=1, dual=1, rho_floor=1e-12, p_floor=0.0, e_floor=table.e_floor)
+        mesh = W.uniform_mesh(2, 1, 1, 8, 1e10, bc=(0, 1, 0))
+        rng = np.random.default_rng(4)
+        U = np.empty(int(mesh.offsets(6)[-1]))
+        for b in range(mesh.nblocks):  # states over five decades in density and two in temperature
+            q = W.unpack_block(mesh, 6, U, b)
+            rho = 10.0 ** rng.uniform(-9, -4, q.shape[1:])
+            e = W.saha_pe(rho, 10.0 ** rng.uniform(4, 6, q.shape[1:]))[1]
+            v = rng.uniform(-1e7, 1e7, (3,) + q.shape[1:])
+            q[0], q[1:4], q[5] = rho, rho * v, rho * e
+            q[4] = q[5] + 0.5 * rho * (v ** 2).sum(0)
+        return cfg, mesh, U
+    return cfg, mesh, W.random_smooth_state(mesh, cfg, 11, amp=0.3)
+
+
+@pytest.mark.parametrize("name", ["one_block", "row_outflow_hlle", "mixed_edges", "table"])
+def test_tile_shapes_on_small_meshes(tdh, orc, saha, name):
+    cfg, mesh, U = _case(name, saha)
+    table = saha if cfg.eos_kind == 1 else None
+    out = {}
+    shapes = tdh.tile_shapes()
+    for t, dims in enumerate(shapes):
+        if dims[0] and any(int(n) % d for n in mesh.blk[:, 0] for d in dims[:3]):
+            continue
+        for mode in (0, 3, 4) if table is not None else (0,):
+            ctx = tdh.Context(cfg, mesh, U, table=table, inv_mode=mode)
+            ctx.set_tile(t)
+            tdh.run_sync_steps(ctx, 3)
+            out[t, mode] = ctx.get_state()
+            ctx.close()
+    split = next(t for t, d in enumerate(shapes) if d[0] == 0)
+    for key, g in out.items():
+        assert np.array_equal(g, out[split, 0]), (key, shapes[key[0]])
+    o, _ = orc.run_sync(cfg, mesh, U, 3, table=table)
+    err = rel_err(cfg.nv, mesh, out[split, 0], o)
+    assert np.all(err <= TOL), err
+
+
+def test_seeds_after_each_stage_are_the_states_cells(tdh, saha):
+    """The cells that modes 2, 3 and 4 hold after steps without a CFL reduction
+    are those of the state (the search in the stage ends at the exact cell)."""
+    cfg, mesh, U = _case("table", saha)
+    cells = []
+    for mode in (2, 3, 4):
+        ctx = tdh.Context(cfg, mesh, U, table=saha, inv_mode=mode)
+        _, dt, _, _ = ctx.reduce_dt()
+        for _ in range(2):
+            ctx.step_level(0, 0.5 * dt)
+        cells.append(ctx.seed_cells())
+        state = ctx.get_state()
+        ctx.close()
+    exact = np.empty(mesh.ncells, dtype=np.int64)
+    k = 0
+    for b in range(mesh.nblocks):
+        q = W.unpack_block(mesh, 6, state, b).reshape(6, -1)
+        kin = 0.5 * (q[1] ** 2 + q[2] ** 2 + q[3] ** 2) / q[0]
+        Uc = q[4] - kin
+        Ue = np.maximum(np.where((Uc > 0) & (Uc > cfg.eta1 * q[4]), Uc, q[5]), q[0] * cfg.e_floor)
+        x = np.clip((np.log10(q[0]) - saha.lr0) / saha.dlr, 0, saha.nrho - 1)
+        i = np.minimum(x.astype(int), saha.nrho - 2)
+        w = x - i
+        col = (1 - w)[:, None] * saha.le[i] + w[:, None] * saha.le[i + 1]
+        j = (col <= np.log10(Ue / q[0])[:, None]).sum(1) - 1
+        exact[k:k + q.shape[1]] = np.clip(j, 0, saha.nT - 2)
+        k += q.shape[1]
+    for c in cells:
+        # a target within rounding of a node may fall to either side
+        assert np.mean(c != exact) < 1e-3 and np.max(np.abs(c - exact)) <= 1
+        assert np.array_equal(c, cells[0])
