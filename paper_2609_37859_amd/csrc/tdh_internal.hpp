@@ -173,9 +173,14 @@ hipError_t mlp_launch_forward(const MlpDev &w, const Seed &s, const double *in, 
                               hipStream_t st);
 hipError_t mlp_launch_fwd_bwd(const MlpDev &w, const Seed &s, const double *in, const double *tgt, int64_t n,
                               int batch, uint64_t seed, int step, int random_batch, float *part, float *loss_part,
-                              float *grad, float *loss, hipStream_t st);
-hipError_t mlp_launch_adam(float *wm, float *m, float *v, const float *g, float lr, float b1, float b2, float eps,
-                           float c1, float c2, hipStream_t st);
+                              hipStream_t st);
+// gradient partials summed into grad (with the loss), or into an Adam step
+// with the refresh of w (loss null: no loss)
+hipError_t mlp_launch_reduce(const float *part, int nparts, float *grad, const float *loss_part, float *loss, int batch,
+                             const MlpDev &w, hipStream_t st);
+hipError_t mlp_launch_adam(const float *part, int nparts, const float *loss_part, float *loss, int batch, float *wm,
+                           float *m, float *v, float lr, float b1, float b2, float eps, float c1, float c2,
+                           const MlpDev &w, hipStream_t st);
 hipError_t mlp_launch_pack(const float *wm, short *w1b, short *w2b, short *w2tb, short *w3b, float *b1, float *b2,
                            float *b3, hipStream_t st);
 

@@ -1455,11 +1455,10 @@ extern "C" tdh_status tdh_mlp_train(tdh_ctx *c, const double *dev_in, const doub
     const int t = ++c->mlp_steps_done;
     const float lr_t = (float)(0.5 * lr * (1.0 + std::cos(M_PI * st / (double)steps)));  // cosine decay
     HIPCHK(c, mlp_launch_fwd_bwd(w, c->seed, dev_in, dev_lT, n, batch, seed, t, 1, c->d_mpart, c->d_mloss_part,
-                                 c->d_mgrad, c->d_mloss + st, c->stream));
+                                 c->stream));
     const float c1 = (float)(1.0 - std::pow((double)b1, t)), c2 = (float)(1.0 - std::pow((double)b2, t));
-    HIPCHK(c, mlp_launch_adam(c->d_mw, c->d_mm, c->d_mv, c->d_mgrad, lr_t, b1, b2, eps, c1, c2, c->stream));
-    HIPCHK(c, mlp_launch_pack(c->d_mw, (short *)w.w1b, (short *)w.w2b, (short *)w.w2tb, (short *)w.w3b, (float *)w.b1,
-                              (float *)w.b2, (float *)w.b3, c->stream));
+    HIPCHK(c, mlp_launch_adam(c->d_mpart, batch / 64, c->d_mloss_part, c->d_mloss + st, batch, c->d_mw, c->d_mm,
+                              c->d_mv, lr_t, b1, b2, eps, c1, c2, w, c->stream));
   }
   if (host_loss)
     HIPCHK(c, hipMemcpyAsync(host_loss, c->d_mloss, steps * sizeof(float), hipMemcpyDeviceToHost, c->stream));
