@@ -20,8 +20,9 @@
 // colour's cells update independently: one thread per cell of the colour,
 // the same values as a sequential sweep, reading and writing its colour's
 // half contiguously and its neighbours from the other half.  Levels are HBM-bound stencils
-// (about 24 bytes per cell and sweep at the finest level); coarse levels are
-// launch-bound, which the host keeps cheap by capturing a cycle in a graph.
+// (about 24 bytes per cell and sweep at the finest level); the levels that fit
+// one workgroup's LDS run there in one launch, and the host captures a cycle in
+// a graph.
 // Sums (mean density, defect norm, mean potential) use a fixed grid and a
 // fixed tree, so they are deterministic.
 #include "tdh_internal.hpp"
@@ -224,61 +225,313 @@ __global__ __launch_bounds__(kMgThreads) void mg_coarse_source_kernel(MgLevel C)
   }
 }
 
-// the coarsest level: `sweeps` red-black sweeps in one workgroup's LDS; with at
-// most 2048 cells every thread owns at most one cell of each colour, whose
-// neighbour slots it finds once
+// ---------------------------------------------------------------------------
+// The V-cycle from the first level of at most kMgLdsTop cells down, in one
+// workgroup's LDS: its sweeps, restrictions, coarse sources, the coarsest
+// level's sweeps, prolongations and post-sweeps, with the values and the order
+// of operations of the level-by-level kernels.  Those levels are too small to
+// fill the chip, and as kernels of their own each of their passes costs a launch
+// of 2 to 5 us (37 launches for 16^3 down to 2^3, 48 of the 64 x 16 x 16 solve's
+// 65 launches per cycle).  A serial chain bounds it: one workgroup, a barrier per
+// colour.  Measured per solve: 64 x 16 x 16 995 -> 664 us, 256^3 9.62 -> 9.20 ms.
+// ---------------------------------------------------------------------------
 constexpr int kMgCoarseMax = 2048;
-__global__ __launch_bounds__(1024) void mg_coarse_solve_kernel(MgLevel C, int sweeps) {
-  __shared__ double sphi[kMgCoarseMax], ssrc[kMgCoarseMax];
-  const int n = (int)ncell(C), half = n >> 1;
-  for (int p = threadIdx.x; p < n; p += 1024) {
-    sphi[p] = C.phi[p];
-    ssrc[p] = C.src[p];
+constexpr int kMgLdsTop = 8192;
+constexpr int kMgLdsDoubles = 20480;  // all 160 KB: potential and source of the top, three arrays below it
+constexpr int kMgLdsLevels = 12;
+constexpr int kMgLdsThreads = 1024;
+
+// A level of the LDS cycle: offsets (in doubles) of its arrays; mx, my: rounded-
+// up 2^32 / hx and 2^32 / ny (row and plane of a cell by one multiplication).
+struct MgLdsLevel {
+  int nx, ny, nz, hx, half;
+  unsigned mx, my;
+  int phi, src, rphi;
+  double hx2, wy, wz, c0, r0;  // r0 = 1 / c0
+};
+struct MgLdsCycle {
+  int n;
+  MgLdsLevel lv[kMgLdsLevels];
+  double *phi;        // the top level's arrays in global memory
+  const double *src;
+};
+
+struct LdsCell {
+  int i, j, k;
+};
+__device__ __forceinline__ LdsCell lds_cell(const MgLdsLevel &L, int r, int color) {
+  const int row = L.hx == 1 ? r : (int)__umulhi((unsigned)r, L.mx);
+  const int k = L.ny == 1 ? row : (int)__umulhi((unsigned)row, L.my);
+  LdsCell c;
+  c.k = k;
+  c.j = row - k * L.ny;
+  c.i = 2 * (r - row * L.hx) + ((c.j + k + color) & 1);
+  return c;
+}
+__device__ __forceinline__ int lds_at(const MgLdsLevel &L, int i, int j, int k) {
+  i = pwrap(i, L.nx);
+  j = pwrap(j, L.ny);
+  k = pwrap(k, L.nz);
+  return ((i + j + k) & 1) * L.half + (((k * L.ny + j) * L.nx + i) >> 1);
+}
+// The six neighbours of cell (i, j, k) are in the other colour's half: along y
+// and z at the same place of their rows, along x one at the cell's own place of
+// the row and the other beside it.
+struct LdsNeighbours {
+  int xm, xp, ym, yp, zm, zp;
+};
+__device__ __forceinline__ LdsNeighbours lds_neighbours(const MgLdsLevel &L, int i, int j, int k) {
+  const int o = ((i + j + k) & 1) ? 0 : L.half;
+  const int ih = i >> 1, row = (k * L.ny + j) * L.hx + o;
+  const int il = (i & 1) ? ih : (ih == 0 ? L.hx - 1 : ih - 1);
+  const int ir = (i & 1) ? (ih == L.hx - 1 ? 0 : ih + 1) : ih;
+  const int sy = L.hx, sz = L.hx * L.ny;
+  LdsNeighbours n;
+  n.xm = row + il;
+  n.xp = row + ir;
+  n.ym = row + ih + (j == 0 ? (L.ny - 1) * sy : -sy);
+  n.yp = row + ih + (j == L.ny - 1 ? -(L.ny - 1) * sy : sy);
+  n.zm = row + ih + (k == 0 ? (L.nz - 1) * sz : -sz);
+  n.zp = row + ih + (k == L.nz - 1 ? -(L.nz - 1) * sz : sz);
+  return n;
+}
+__device__ __forceinline__ double lds_nbsum(const MgLdsLevel &L, const double *f, const LdsNeighbours &n) {
+#pragma clang fp contract(off)
+  const double sx = f[n.xm] + f[n.xp];
+  const double sy = f[n.ym] + f[n.yp];
+  const double sz = f[n.zm] + f[n.zp];
+  return (sx + L.wy * sy) + L.wz * sz;
+}
+__device__ __forceinline__ double lds_nbsum(const MgLdsLevel &L, const double *f, int i, int j, int k) {
+  return lds_nbsum(L, f, lds_neighbours(L, i, j, k));
+}
+// x / c0 by the reciprocal and one correction: the rounded quotient in three
+// dependent operations instead of a division's eleven
+__device__ __forceinline__ double over_c0(double c0, double r0, double x) {
+  const double q = x * r0;
+  return fma(fma(-c0, q, x), r0, q);
+}
+__device__ __forceinline__ double lds_apply(const MgLdsLevel &L, const double *f, int i, int j, int k) {
+#pragma clang fp contract(off)
+  return (L.c0 * f[lds_at(L, i, j, k)] - lds_nbsum(L, f, i, j, k)) / L.hx2;
+}
+
+__device__ __forceinline__ void lds_sweep(const MgLdsLevel &L, double *lds) {
+  double *phi = lds + L.phi;
+  const double *src = lds + L.src;
+  for (int color = 0; color < 2; ++color) {
+    for (int r = threadIdx.x; r < L.half; r += kMgLdsThreads) {
+#pragma clang fp contract(off)
+      const LdsCell c = lds_cell(L, r, color);
+      const int q = color * L.half + r;
+      const double gs = over_c0(L.c0, L.r0, lds_nbsum(L, phi, c.i, c.j, c.k) + L.hx2 * src[q]);
+      phi[q] = (1.0 - kOmegaGS) * phi[q] + kOmegaGS * gs;
+    }
+    __syncthreads();
   }
-  const bool own = (int)threadIdx.x < half;
-  int q[2] = {0, 0}, nb[2][6];
-  if (own) {
+}
+
+// Restriction of level L to C (as mg_restrict_kernel, then mg_coarse_source_kernel).
+__device__ __forceinline__ void lds_restrict(const MgLdsLevel &L, const MgLdsLevel &C, double *lds) {
+#pragma clang fp contract(off)
+  const double *f = lds + L.phi, *src = lds + L.src;
+  auto defect = [&](int i, int j, int k) { return src[lds_at(L, i, j, k)] - lds_apply(L, f, i, j, k); };
+  for (int q = threadIdx.x; q < 2 * C.half; q += kMgLdsThreads) {
+    const LdsCell c = lds_cell(C, q >= C.half ? q - C.half : q, q >= C.half);
+    const int I = 2 * c.i, J = 2 * c.j, K = 2 * c.k;
+    double m[2][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = J + (e & 1), k = K + (e >> 1);
+      m[0][e] = f[lds_at(L, I, j, k)] + f[lds_at(L, I + 1, j, k)];
+      m[1][e] = defect(I, j, k) + defect(I + 1, j, k);
+    }
+    const double r = 0.125 * ((m[0][0] + m[0][1]) + (m[0][2] + m[0][3]));
+    lds[C.phi + q] = r;
+    lds[C.rphi + q] = r;
+    lds[C.src + q] = 0.125 * ((m[1][0] + m[1][1]) + (m[1][2] + m[1][3]));
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < 2 * C.half; q += kMgLdsThreads) {
+    const LdsCell c = lds_cell(C, q >= C.half ? q - C.half : q, q >= C.half);
+    lds[C.src + q] = lds[C.src + q] + lds_apply(C, lds + C.phi, c.i, c.j, c.k);
+  }
+  __syncthreads();
+}
+
+// Tricubic prolongation of the correction of C onto L (as mg_prolong_kernel).
+__device__ __forceinline__ void lds_prolong(const MgLdsLevel &L, const MgLdsLevel &C, double *lds) {
+  const double w[2][4] = {{-5.0 / 128.0, 35.0 / 128.0, 105.0 / 128.0, -7.0 / 128.0},
+                          {-7.0 / 128.0, 105.0 / 128.0, 35.0 / 128.0, -5.0 / 128.0}};
+  for (int q = threadIdx.x; q < 2 * C.half; q += kMgLdsThreads) lds[C.rphi + q] = lds[C.phi + q] - lds[C.rphi + q];
+  __syncthreads();
+  const double *e = lds + C.rphi;
+  double *phi = lds + L.phi;
+  for (int q = threadIdx.x; q < 4 * C.half; q += kMgLdsThreads) {
+    // a coarse cell and the z side of its children
+    const int cz = q >= 2 * C.half, p = q - (cz ? 2 * C.half : 0);
+    const LdsCell c = lds_cell(C, p >= C.half ? p - C.half : p, p >= C.half);
+    int xs[5];
+#pragma unroll
+    for (int ox = 0; ox < 5; ++ox) xs[ox] = pwrap(c.i + ox - 2, C.nx);
+    double Z[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+#pragma unroll 1
+    for (int oz = 0; oz < 4; ++oz) {
+      double Y[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+#pragma unroll
+      for (int oy = 0; oy < 5; ++oy) {
+        const int j = pwrap(c.j + oy - 2, C.ny), k = pwrap(c.k + oz + cz - 2, C.nz);
+        const int row = (k * C.ny + j) * C.hx, par = j + k;
+        double v[5];
+#pragma unroll
+        for (int ox = 0; ox < 5; ++ox) {
+          const int i = xs[ox];
+          v[ox] = e[((i + par) & 1) * C.half + row + (i >> 1)];
+        }
+#pragma unroll
+        for (int cx = 0; cx < 2; ++cx) {
+          double sx = 0.0;
+#pragma unroll
+          for (int a = 0; a < 4; ++a) sx += w[cx][a] * v[cx + a];
+#pragma unroll
+          for (int cy = 0; cy < 2; ++cy) {
+            const int b = oy - cy;
+            if (b >= 0 && b <= 3) Y[cy][cx] += w[cy][b] * sx;
+          }
+        }
+      }
+      const double wz = cz ? (oz == 0 ? w[1][0] : (oz == 1 ? w[1][1] : (oz == 2 ? w[1][2] : w[1][3])))
+                           : (oz == 0 ? w[0][0] : (oz == 1 ? w[0][1] : (oz == 2 ? w[0][2] : w[0][3])));
+#pragma unroll
+      for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+        for (int cx = 0; cx < 2; ++cx) Z[cy][cx] += wz * Y[cy][cx];
+    }
+#pragma unroll
+    for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) phi[lds_at(L, 2 * c.i + cx, 2 * c.j + cy, 2 * c.k + cz)] += Z[cy][cx];
+  }
+  __syncthreads();
+}
+
+// The coarsest level's sweeps: at most 2048 cells, so every thread owns at most
+// one cell of each colour, whose neighbour slots it finds once.  Up to 64 cells
+// of a colour one wave sweeps alone, without barriers.
+__device__ __forceinline__ void lds_coarse_solve(const MgLdsLevel &C, int sweeps, double *lds) {
+#pragma clang fp contract(off)
+  double *phi = lds + C.phi;
+  const int half = C.half;
+  const bool one_wave = half <= 64;
+  if (!one_wave || threadIdx.x < 64) {
+    const bool own = (int)threadIdx.x < half;
+    const int t = own ? (int)threadIdx.x : 0;
+    LdsNeighbours nb[2];
+    double hs[2], old[2];
 #pragma unroll
     for (int color = 0; color < 2; ++color) {
-      int i, j, k;
-      q[color] = color * half + threadIdx.x;
-      cell_of(C, q[color], i, j, k);
-      nb[color][0] = (int)at(C, i - 1, j, k);
-      nb[color][1] = (int)at(C, i + 1, j, k);
-      nb[color][2] = (int)at(C, i, j - 1, k);
-      nb[color][3] = (int)at(C, i, j + 1, k);
-      nb[color][4] = (int)at(C, i, j, k - 1);
-      nb[color][5] = (int)at(C, i, j, k + 1);
+      const LdsCell c = lds_cell(C, t, color);
+      nb[color] = lds_neighbours(C, c.i, c.j, c.k);
+      hs[color] = C.hx2 * lds[C.src + color * half + t];
+      old[color] = phi[color * half + t];
+    }
+    for (int s = 0; s < sweeps; ++s) {
+#pragma unroll
+      for (int color = 0; color < 2; ++color) {
+        const double gs = over_c0(C.c0, C.r0, lds_nbsum(C, phi, nb[color]) + hs[color]);
+        old[color] = (1.0 - kOmegaGS) * old[color] + kOmegaGS * gs;
+        if (own) phi[color * half + t] = old[color];
+        if (one_wave) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        else __syncthreads();
+      }
     }
   }
   __syncthreads();
-  for (int s = 0; s < sweeps; ++s) {
+}
+
+// The coarsest level's sweeps are one linear map of its potential and source,
+// but each sweep is a chain of two dependent passes (0.23 us; 2 x 2 x 2 cells
+// take 72 of them, 8 x 2 x 2 cells 288).  Up to kMgMatCells cells the map's
+// matrix is found once per solve, each column by the sweeps of a unit vector on
+// its own compute unit, and a cycle multiplies by it: 55 us per solve and 27 us
+// per cycle where the sweeps take 90 us per cycle (64 x 16 x 16; with 2 x 2 x 2
+// cells 62 and 48 us).  128 cells and more would need 4 times the matrix and
+// gain less, each sweep spreading over more threads.
+//   mat: [2 n] columns of n (potential, then source)
+constexpr int kMgMatCells = 64;
+constexpr int kMgMatThreads = 512;  // that multiply; 2 n columns over 512 / n groups of threads: at most 16 each
+__global__ __launch_bounds__(64) void mg_coarse_matrix_kernel(MgLdsLevel C, int sweeps, double *mat) {
+  __shared__ double lds[2 * kMgMatCells];
+  const int n = 2 * C.half;
+  for (int q = threadIdx.x; q < 2 * n; q += 64) lds[q] = q == (int)blockIdx.x ? 1.0 : 0.0;
+  __syncthreads();
+  C.phi = 0;
+  C.src = n;
+  lds_coarse_solve(C, sweeps, lds);
+  for (int q = threadIdx.x; q < n; q += 64) mat[(long long)blockIdx.x * n + q] = lds[q];
+}
+
+// phi = mat (phi, src): the 2 n columns are shared among kMgMatThreads threads
+// (n of them per group of columns) and the groups' sums added in order; red:
+// kMgMatThreads doubles of LDS.
+__device__ __forceinline__ void lds_coarse_apply(const MgLdsLevel &C, const double *m, double *lds, double *red) {
+  const int n = 2 * C.half, groups = kMgMatThreads / n;
+  const int q = (int)threadIdx.x % n, g = (int)threadIdx.x / n;
+  if (g < groups) {
+    double s = 0.0;
 #pragma unroll
-    for (int color = 0; color < 2; ++color) {
-      if (own) {
-#pragma clang fp contract(off)
-        const int *g = nb[color];
-        const double sx = sphi[g[0]] + sphi[g[1]];
-        const double sy = sphi[g[2]] + sphi[g[3]];
-        const double sz = sphi[g[4]] + sphi[g[5]];
-        const double nbs = (sx + C.wy * sy) + C.wz * sz;
-        const double gs = (nbs + C.hx2 * ssrc[q[color]]) / C.c0;
-        sphi[q[color]] = (1.0 - kOmegaGS) * sphi[q[color]] + kOmegaGS * gs;
-      }
-      __syncthreads();
+    for (int k = 0; k < kMgMatCells / 4; ++k) {
+      const int c = g + k * groups;
+      if (c < 2 * n) s = fma(m[k], lds[(c < n ? C.phi : C.src - n) + c], s);
+    }
+    red[threadIdx.x] = s;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < n) {
+    double s = red[threadIdx.x];
+    for (int k = 1; k < groups; ++k) s += red[k * n + threadIdx.x];
+    lds[C.phi + threadIdx.x] = s;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kMgLdsThreads) void mg_lds_cycle_kernel(MgLdsCycle P, int sweeps, const double *mat) {
+  __shared__ double lds[kMgLdsDoubles];
+  const MgLdsLevel &B = P.lv[P.n - 1];
+  const int nb = 2 * B.half;
+  // this thread's share of the coarsest level's matrix, on its way from the start
+  double m[kMgMatCells / 4];
+  if (mat) {
+    const int groups = kMgMatThreads / nb, q = (int)threadIdx.x % nb, g = (int)threadIdx.x / nb;
+#pragma unroll
+    for (int k = 0; k < kMgMatCells / 4; ++k) {
+      const int c = g + k * groups;
+      m[k] = g < groups && c < 2 * nb ? mat[c * nb + q] : 0.0;
     }
   }
-  for (int p = threadIdx.x; p < n; p += 1024) C.phi[p] = sphi[p];
+  const int n0 = 2 * P.lv[0].half;
+  for (int q = threadIdx.x; q < n0; q += kMgLdsThreads) {
+    lds[P.lv[0].phi + q] = P.phi[q];
+    lds[P.lv[0].src + q] = P.src[q];
+  }
+  __syncthreads();
+  for (int l = 0; l + 1 < P.n; ++l) {
+    lds_sweep(P.lv[l], lds);
+    lds_sweep(P.lv[l], lds);
+    lds_restrict(P.lv[l], P.lv[l + 1], lds);
+  }
+  if (mat) lds_coarse_apply(B, m, lds, lds + kMgLdsDoubles - kMgMatThreads);
+  else lds_coarse_solve(B, sweeps, lds);
+  for (int l = P.n - 2; l >= 0; --l) {
+    lds_prolong(P.lv[l], P.lv[l + 1], lds);
+    lds_sweep(P.lv[l], lds);
+    lds_sweep(P.lv[l], lds);
+  }
+  for (int q = threadIdx.x; q < n0; q += kMgLdsThreads) P.phi[q] = lds[P.lv[0].phi + q];
 }
 
-// correction (coarse result - R phi), in place of rphi
-__global__ __launch_bounds__(kMgThreads) void mg_correction_kernel(MgLevel C) {
-  const long long n = ncell(C);
-  for (long long p = blockIdx.x * (long long)kMgThreads + threadIdx.x; p < n; p += (long long)gridDim.x * kMgThreads)
-    C.rphi[p] = C.phi[p] - C.rphi[p];
-}
-
-// fine phi += tricubic interpolation of the coarse correction: per axis the
+// fine phi += tricubic interpolation of the coarse correction (coarse result -
+// R phi, formed where it is read): per axis the
 // cubic through the four nearest coarse centres, weights (-5, 35, 105, -7)/128
 // for the child at -1/4 of its parent (centres parent-2 .. parent+1) and
 // (-7, 105, 35, -5)/128 for the child at +1/4 (parent-1 .. parent+2), summed
@@ -301,7 +554,10 @@ __global__ __launch_bounds__(kMgThreads) void mg_prolong_kernel(MgLevel F, MgLev
       for (int oy = 0; oy < 5; ++oy) {
         double e[5];
 #pragma unroll
-        for (int ox = 0; ox < 5; ++ox) e[ox] = C.rphi[at(C, i + ox - 2, j + oy - 2, k + oz - 2)];
+        for (int ox = 0; ox < 5; ++ox) {
+          const long long c = at(C, i + ox - 2, j + oy - 2, k + oz - 2);
+          e[ox] = C.phi[c] - C.rphi[c];
+        }
         double X[2];
 #pragma unroll
         for (int cx = 0; cx < 2; ++cx) {
@@ -340,7 +596,7 @@ __global__ __launch_bounds__(kMgThreads) void mg_prolong_kernel(MgLevel F, MgLev
 }
 
 // The same prolongation by tiles: a workgroup takes 8 x 8 x 4 coarse cells
-// (natural order, one per thread), stages their restricted potential with a
+// (natural order, one per thread), stages their correction with a
 // two-cell halo in LDS once (12 x 12 x 8 values, against 125 gathers per cell
 // with a wrapped red-black index each), then forms each cell's eight children
 // from LDS with the same products and sums in the same order as
@@ -361,7 +617,8 @@ __global__ __launch_bounds__(kMgThreads) void mg_prolong_tiled_kernel(MgLevel F,
     __syncthreads();  // the previous tile's reads are done
     for (int v = threadIdx.x; v < HX * HY * HZ; v += kMgThreads) {
       const int a = v % HX, b = (v / HX) % HY, c = v / (HX * HY);
-      sc[c][b][a] = C.rphi[at(C, i0 + a - 2, j0 + b - 2, k0 + c - 2)];
+      const long long q = at(C, i0 + a - 2, j0 + b - 2, k0 + c - 2);
+      sc[c][b][a] = C.phi[q] - C.rphi[q];
     }
     __syncthreads();
     double Z[2][2][2] = {{{0.0, 0.0}, {0.0, 0.0}}, {{0.0, 0.0}, {0.0, 0.0}}};  // [cz][cy][cx]
@@ -474,14 +731,70 @@ hipError_t mg_launch_restrict(const MgLevel &F, const MgLevel &C, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t mg_launch_coarse_solve(const MgLevel &C, int sweeps, hipStream_t s) {
-  if ((long long)C.nx * C.ny * C.nz > kMgCoarseMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(mg_coarse_solve_kernel, dim3(1), dim3(1024), 0, s, C, sweeps);
+static MgLdsLevel lds_level(const MgLevel &g) {
+  MgLdsLevel L{};
+  L.nx = g.nx; L.ny = g.ny; L.nz = g.nz;
+  L.hx = L.nx / 2;
+  L.half = g.nx * g.ny * g.nz / 2;
+  L.mx = (unsigned)(((1ULL << 32) + L.hx - 1) / L.hx);
+  L.my = (unsigned)(((1ULL << 32) + L.ny - 1) / L.ny);
+  L.hx2 = g.hx2; L.wy = g.wy; L.wz = g.wz; L.c0 = g.c0; L.r0 = 1.0 / L.c0;
+  return L;
+}
+
+// doubles of LDS the V-cycle from level lv[0] down takes (the coarsest level's
+// product adds one per multiplying thread)
+static long long lds_doubles(const MgLevel *lv, int n) {
+  long long d = kMgMatThreads;
+  for (int k = 0; k < n; ++k) d += (k ? 3 : 2) * ((long long)lv[k].nx * lv[k].ny * lv[k].nz);
+  return d;
+}
+
+// the first of levels 0 .. nlev-1 from which the rest of the V-cycle fits the LDS kernel
+int mg_lds_top(const MgLevel *lv, int nlev) {
+  for (int l = 0; l < nlev; ++l)
+    if ((long long)lv[l].nx * lv[l].ny * lv[l].nz <= kMgLdsTop && lds_doubles(lv + l, nlev - l) <= kMgLdsDoubles &&
+        nlev - l <= kMgLdsLevels)
+      return l;
+  return nlev - 1;
+}
+
+// doubles of the coarsest level's matrix (0: its sweeps run in every cycle)
+int mg_coarse_matrix_doubles(const MgLevel &C) {
+  const long long n = (long long)C.nx * C.ny * C.nz;
+  return n <= kMgMatCells ? (int)(2 * n * n) : 0;
+}
+
+hipError_t mg_launch_coarse_matrix(const MgLevel &C, int sweeps, double *mat, hipStream_t s) {
+  const int n = C.nx * C.ny * C.nz;
+  if (n > kMgMatCells) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mg_coarse_matrix_kernel, dim3(2 * n), dim3(64), 0, s, lds_level(C), sweeps, mat);
+  return hipGetLastError();
+}
+
+hipError_t mg_launch_lds_cycle(const MgLevel *lv, int n, int sweeps, const double *mat, hipStream_t s) {
+  const MgLevel &C = lv[n - 1];
+  if (n < 1 || n > kMgLdsLevels || (long long)C.nx * C.ny * C.nz > kMgCoarseMax || lds_doubles(lv, n) > kMgLdsDoubles)
+    return hipErrorInvalidValue;
+  MgLdsCycle P{};
+  P.n = n;
+  P.phi = lv[0].phi;
+  P.src = lv[0].src;
+  int off = 0;
+  for (int l = 0; l < n; ++l) {
+    MgLdsLevel &L = P.lv[l];
+    L = lds_level(lv[l]);
+    const int cells = 2 * L.half;
+    L.phi = off;
+    L.src = off + cells;
+    L.rphi = l ? off + 2 * cells : 0;
+    off += (l ? 3 : 2) * cells;
+  }
+  hipLaunchKernelGGL(mg_lds_cycle_kernel, dim3(1), dim3(kMgLdsThreads), 0, s, P, sweeps, mat);
   return hipGetLastError();
 }
 
 hipError_t mg_launch_prolong(const MgLevel &F, const MgLevel &C, hipStream_t s) {
-  hipLaunchKernelGGL(mg_correction_kernel, dim3(grid_for((long long)C.nx * C.ny * C.nz)), dim3(kMgThreads), 0, s, C);
   if (C.nx % kPtx == 0 && C.ny % kPty == 0 && C.nz % kPtz == 0) {
     const int tiles = (C.nx / kPtx) * (C.ny / kPty) * (C.nz / kPtz);
     hipLaunchKernelGGL(mg_prolong_tiled_kernel, dim3(tiles < 4096 ? tiles : 4096), dim3(kMgThreads), 0, s, F, C);

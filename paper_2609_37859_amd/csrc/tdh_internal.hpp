@@ -134,7 +134,12 @@ hipError_t mg_launch_affine(double *x, const double *shift, double fill, long lo
 hipError_t mg_launch_sweep(const MgLevel &L, hipStream_t s);
 hipError_t mg_launch_defect_norm(const MgLevel &L, double *part, double *out, hipStream_t s);  // RMS defect
 hipError_t mg_launch_restrict(const MgLevel &F, const MgLevel &C, hipStream_t s);
-hipError_t mg_launch_coarse_solve(const MgLevel &C, int sweeps, hipStream_t s);
+// the V-cycle from a level down in one launch: levels lv[0..n-1], the last the coarsest
+int mg_lds_top(const MgLevel *lv, int nlev);
+// (sweeps of the coarsest, or its matrix as mg_launch_coarse_matrix leaves it)
+hipError_t mg_launch_lds_cycle(const MgLevel *lv, int n, int sweeps, const double *mat, hipStream_t s);
+int mg_coarse_matrix_doubles(const MgLevel &C);
+hipError_t mg_launch_coarse_matrix(const MgLevel &C, int sweeps, double *mat, hipStream_t s);
 hipError_t mg_launch_prolong(const MgLevel &F, const MgLevel &C, hipStream_t s);
 hipError_t mg_launch_scatter(const MeshDev &m, int nblocks, int nmax, const MgLevel &F, double *phib, hipStream_t s);
 int mg_coarse_max();

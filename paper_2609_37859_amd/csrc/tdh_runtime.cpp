@@ -1000,8 +1000,14 @@ extern "C" tdh_status tdh_get_state(tdh_ctx *c, double *host) {
 namespace {
 struct MgPlan {
   int nlev = 0;
+  int lds_top = 0;  // first level of the part that runs in one workgroup's LDS
   MgLevel lv[kMgMaxLevels];
   double *part = nullptr, *scal = nullptr;  // sum partials; mean density, defect norm, mean potential
+  double *mat = nullptr;                    // the coarsest level's sweeps as a matrix (null: too many cells)
+  int coarse_sweeps() const {
+    const int t = lv[nlev - 1].nx + lv[nlev - 1].ny + lv[nlev - 1].nz;
+    return 2 * t * t;
+  }
   size_t bytes = 0;
 };
 }  // namespace
@@ -1035,6 +1041,7 @@ static tdh_status mg_plan(tdh_ctx *c, char *base, MgPlan *P) {
     return fail(c, TDH_ERANGE, "coarsest multigrid level %d x %d x %d exceeds %d cells", Cl.nx, Cl.ny, Cl.nz,
                 mg_coarse_max());
   P->nlev = nlev;
+  P->lds_top = mg_lds_top(P->lv, nlev);
   size_t off = 0;  // doubles
   auto take = [&](long long n) { double *p = base ? (double *)base + off : nullptr; off += (size_t)((n + 31) & ~31LL); return p; };
   for (int l = 0; l < nlev; ++l) {
@@ -1046,6 +1053,8 @@ static tdh_status mg_plan(tdh_ctx *c, char *base, MgPlan *P) {
   }
   P->part = take(kMgSumParts);
   P->scal = take(4);
+  const int nmat = mg_coarse_matrix_doubles(P->lv[nlev - 1]);
+  P->mat = nmat ? take(nmat) : nullptr;
   P->bytes = off * sizeof(double);
   return TDH_OK;
 }
@@ -1053,10 +1062,7 @@ static tdh_status mg_plan(tdh_ctx *c, char *base, MgPlan *P) {
 static hipError_t mg_vcycle(const MgPlan &P, int l, hipStream_t s) {
   hipError_t e;
   const MgLevel &L = P.lv[l];
-  if (l == P.nlev - 1) {
-    const int t = L.nx + L.ny + L.nz;
-    return mg_launch_coarse_solve(L, 2 * t * t, s);
-  }
+  if (l == P.lds_top) return mg_launch_lds_cycle(P.lv + l, P.nlev - l, P.coarse_sweeps(), P.mat, s);
   const MgLevel &C = P.lv[l + 1];
   if ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)) || (e = mg_launch_restrict(L, C, s)) || (e = mg_vcycle(P, l + 1, s)) || (e = mg_launch_prolong(L, C, s)) ||
       (e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)))
@@ -1120,6 +1126,7 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
   };
   int cyc = 0;
   while (cyc < max_cycles && !(d <= tol)) {
+    if (cyc == 0 && P.mat) HIPCHK(c, mg_launch_coarse_matrix(P.lv[P.nlev - 1], P.coarse_sweeps(), P.mat, s));
     auto it = c->mg_graphs.find(dev_work);
     if (it == c->mg_graphs.end()) {
       HIPCHK(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));

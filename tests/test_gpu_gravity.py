@@ -67,6 +67,23 @@ def test_vcycles_mixed_blocks_anisotropic(tdh, orc):
     ctx.close()
 
 
+@pytest.mark.parametrize("blocks, n, dx", [
+    ((1, 1, 1), 8, (0.1, 0.1, 0.1)),       # every level in LDS, coarsest 2 x 2 x 2
+    ((4, 1, 1), 8, (0.1, 0.15, 0.12)),     # coarsest 8 x 2 x 2, anisotropic
+    ((3, 2, 1), 8, (0.1, 0.1, 0.1)),       # 48 cells: the matrix's columns divide unevenly
+    ((4, 2, 1), 8, (0.1, 0.1, 0.1)),       # 64 cells: the largest matrix
+    ((16, 1, 1), 8, (0.1, 0.1, 0.1)),      # coarsest of 128 cells: swept, 64 of a colour by one wave
+    ((3, 5, 1), 8, (0.1, 0.1, 0.1)),       # 120 coarsest cells, rows of 3 pairs
+    ((15, 17, 1), 8, (0.1, 0.1, 0.1)),     # 2040 coarsest cells: the only level in LDS
+    ((4, 2, 2), 16, (0.1, 0.1, 0.1)),      # the LDS part starts at its largest level, 32 x 16 x 16
+])
+def test_coarse_levels_in_one_workgroup(tdh, orc, blocks, n, dx):
+    mesh = W.uniform_mesh(*blocks, n, dx)
+    cfg, U, phi0 = _density_state(mesh, 6)
+    ctx, _ = _compare(tdh, orc, mesh, cfg, U, phi0, 1.5, 3)
+    ctx.close()
+
+
 def test_warm_start_and_tolerance(tdh, orc):
     mesh = W.uniform_mesh(2, 2, 2, 16, 1.0 / 32)
     cfg, U, phi0 = _density_state(mesh, 5)
