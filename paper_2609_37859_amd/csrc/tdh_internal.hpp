@@ -56,7 +56,14 @@ struct Table {
   // -log10 c_i} with c_i = 1 / (1 + (i + 1/2)/128), i < 128; ex[j] = 2^(j/64), j < 64.
   const double2 *lg;
   const double *ex;
+  // Start cells of a search without a seed: guess[i][b] is the cell of the
+  // centre of bin b (of nbins over the table's range of log e) on the mean of
+  // density rows i and i+1.
+  const unsigned short *guess;
+  int nbins;
+  double g0, inv_dg;  // log e of the first bin's lower edge, bins per unit
 };
+constexpr int kGuessBinsPerCell = 2;
 
 constexpr int kMlpParams = 4417;  // W1[64][2], b1[64], W2[64][64], b2[64], W3[64], b3
 

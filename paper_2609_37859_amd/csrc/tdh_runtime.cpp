@@ -555,9 +555,9 @@ extern "C" tdh_status tdh_init_blocks(tdh_ctx *c, const tdh_mesh *m, void *dev_a
 
 // Packed EOS table (see Table in tdh_internal.hpp), in doubles: density-row
 // pairs of log e, then of (log P, log c_s^2), then the 128-byte cell records,
-// then the log10 and 10^x function tables.
+// then the log10 and 10^x function tables, then the searches' start cells.
 struct TableLayout {
-  size_t pc_off, rec_off, fn_off, total;
+  size_t pc_off, rec_off, fn_off, guess_off, total;
 };
 static TableLayout table_layout(int nrho, int nT) {
   TableLayout t;
@@ -566,7 +566,8 @@ static TableLayout table_layout(int nrho, int nT) {
   t.rec_off = (t.pc_off + 4 * np + 15) & ~(size_t)15;  // 128-byte cell records
   const size_t nrec = (size_t)(nrho - 1) * (nT - 1);
   t.fn_off = t.rec_off + 16 * nrec;                    // 128-byte aligned
-  t.total = t.fn_off + 2 * 128 + 64;
+  t.guess_off = t.fn_off + 2 * 128 + 64;
+  t.total = t.guess_off + ((size_t)(nrho - 1) * kGuessBinsPerCell * nT + 3) / 4;  // 16-bit cells
   return t;
 }
 
@@ -625,6 +626,25 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
         r[8 + v] = packed[pc_off + 4 * (q + 1) + v];
       }
     }
+  // start cells: one walk up each row pair's mean column
+  double lo = le[0], hi = le[nT - 1];
+  for (int i = 1; i < nrho; ++i) {
+    lo = std::min(lo, le[(size_t)i * nT]);
+    hi = std::max(hi, le[(size_t)i * nT + nT - 1]);
+  }
+  const int nbins = kGuessBinsPerCell * nT;
+  const double dg = (hi - lo) / nbins;
+  const bool binned = std::isfinite(dg) && dg > 0.0 && std::isfinite(1.0 / dg);  // else every search starts in bin 0
+  unsigned short *guess = (unsigned short *)(packed.data() + TL.guess_off);
+  for (int i = 0; i + 1 < nrho; ++i) {
+    const double *r0 = le + (size_t)i * nT, *r1 = r0 + nT;
+    int j = 0;
+    for (int b = 0; b < nbins && binned; ++b) {
+      const double x = lo + (b + 0.5) * dg;
+      while (j < nT - 2 && 0.5 * (r0[j + 1] + r1[j + 1]) <= x) ++j;
+      guess[(size_t)i * nbins + b] = (unsigned short)j;
+    }
+  }
   c->d_table = (double *)dev_table;
   HIPCHK(c, hipMemcpyAsync(c->d_table, packed.data(), packed.size() * sizeof(double), hipMemcpyHostToDevice,
                            c->stream));
@@ -641,6 +661,10 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   c->tab.rec = c->d_table + rec_off;
   c->tab.lg = (const double2 *)(c->d_table + fn_off);
   c->tab.ex = c->d_table + fn_off + 256;
+  c->tab.guess = (const unsigned short *)(c->d_table + TL.guess_off);
+  c->tab.nbins = nbins;
+  c->tab.g0 = binned ? lo : 0.0;
+  c->tab.inv_dg = binned ? 1.0 / dg : 0.0;
   c->have_table = true;
   c->seeds_held = false;  // cells of another table
   c->cfl_parts = false;
