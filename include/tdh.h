@@ -250,8 +250,11 @@ tdh_status tdh_set_state(tdh_ctx *ctx, const double *host_state);
  * are at least 4, and every level, the coarsest included, has even
  * dimensions; the coarsest level holds at most 2048 cells (TDH_EINVAL /
  * TDH_ERANGE otherwise).  Only between windows (TDH_ESTATE).
- * dev_work: caller-owned device buffer of at least the bytes
- * tdh_gravity_workspace_bytes returns; its first nx*ny*nz doubles hold the
+ * dev_work: caller-owned device buffer of the bytes
+ * tdh_gravity_workspace_bytes returns (one that holds the levels' potentials,
+ * sources and restricted potentials only, without the second potentials of
+ * levels of 2^20 cells and more and the coarsest level's matrix, serves too, by
+ * slower passes; a smaller one is TDH_ENOMEM); its first nx*ny*nz doubles hold the
  * solution on the global grid in red-black order (the cells with i+j+k even
  * first, then the others, each half [nz][ny][nx/2] with x fastest), the start
  * of the next solve when warm != 0 (pass the same buffer again); warm == 0

@@ -68,6 +68,12 @@ __device__ __forceinline__ double nbsum(const MgLevel &L, const double *f, int i
   return (sx + L.wy * sy) + L.wz * sz;
 }
 
+// x / c0 by the reciprocal and one correction: the rounded quotient in three
+// dependent operations instead of a division's eleven
+__device__ __forceinline__ double over_c0(double c0, double r0, double x) {
+  const double q = x * r0;
+  return fma(fma(-c0, q, x), r0, q);
+}
 __device__ __forceinline__ double apply_A(const MgLevel &L, const double *f, int i, int j, int k) {
 #pragma clang fp contract(off)
   return (L.c0 * f[at(L, i, j, k)] - nbsum(L, f, i, j, k)) / L.hx2;
@@ -190,6 +196,141 @@ __global__ __launch_bounds__(kMgThreads) void mg_defect_sq_partial_kernel(MgLeve
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
+// ---------------------------------------------------------------------------
+// Red-black sweeps of a large level in one pass over memory: S half-sweeps (two
+// or four) from L.phi to `out`, and with NORM the squared defect of the result.
+// One colour's kernel reads and writes four half-arrays, so that two sweeps move
+// eight times the level's potential and the defect twice more; here they move
+// three (potential and source in, potential out) and the halo.  A workgroup
+// holds 32 x 32 columns of cell pairs (one red, one black) and marches along z:
+// in step z it loads plane z and updates plane z - s by half-sweep s, each from
+// the previous half-sweep's three planes in registers and its plane's neighbours
+// in LDS, published one step before; one barrier per plane.  A half-sweep spoils
+// one more cell at the columns' edge, which the tiles overlap by (28 x 24 pairs
+// of the 32 x 32 are written by two sweeps, 28 x 26 by one with the defect), and
+// one more plane at the ends of a z chunk.  The values are the one-colour
+// kernel's, the defect's sum is taken in another order.
+// 256^3: two sweeps 131 us against 250, a sweep and the defect 104 us against 258;
+// registers held to 64 for two workgroups on a compute unit spill (twice as slow).
+// Levels of 2^20 cells and more: ten cycles of 256^3 12.7 -> 9.0 ms, 128^3 3.24 ->
+// 2.68, 128 x 128 x 64 2.50 -> 2.19; below, the tiles and z chunks are too few to
+// pay for their edges (64^3 1.74 ms plain, 1.77 this way; 128 x 64 x 32 1.70, 1.78).
+// ---------------------------------------------------------------------------
+constexpr int kMgSmoothThreads = 1024, kMgEdge = 32;
+constexpr long long kMgSmoothCells = 1 << 20;
+template <int S, bool NORM>
+struct MgSmooth {
+  static constexpr int H = S + (NORM ? 1 : 0);               // spoiled cells at every edge
+  static constexpr int PX = (H + 1) / 2, PY = H;             // in pairs and rows
+  static constexpr int OX = kMgEdge - 2 * PX, OY = kMgEdge - 2 * PY;
+};
+
+__device__ __forceinline__ int modulo(int a, int n) {
+  a %= n;
+  return a < 0 ? a + n : a;
+}
+
+template <int S, bool NORM>
+__global__ __launch_bounds__(kMgSmoothThreads) void mg_smooth_kernel(MgLevel L, double *out, int tx, int ty, int nc,
+                                                                     double *part) {
+#pragma clang fp contract(off)
+  using G = MgSmooth<S, NORM>;
+  static_assert((S == 2 || S == 4) && !(S == 4 && NORM), "the planes kept below");
+  __shared__ double sh[2][4][kMgSmoothThreads];
+  // workgroups of one XCD take consecutive tiles: neighbours share its L2
+  const int per = gridDim.x / 8, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (id >= tx * ty * nc) return;
+  const int ti = id % tx, tj = (id / tx) % ty, tc = id / (tx * ty);
+  const int k0 = (int)((long long)L.nz * tc / nc), k1 = (int)((long long)L.nz * (tc + 1) / nc);
+  const int t = threadIdx.x, lane = t & (kMgEdge - 1), row = t / kMgEdge;
+  const int hx = L.nx >> 1;
+  const int pi = ti * G::OX + lane - G::PX, pj = tj * G::OY + row - G::PY;
+  const bool mine = lane >= G::PX && lane < kMgEdge - G::PX && row >= G::PY && row < kMgEdge - G::PY && pi < hx &&
+                    pj < L.ny;
+  const int j = modulo(pj, L.ny);
+  const long long plane = (long long)hx * L.ny, half = ncell(L) >> 1;
+  const long long col = (long long)j * hx + modulo(pi, hx);
+  // neighbours in the plane: the edge's own value beyond the columns (spoiled cells)
+  const int tl = lane ? t - 1 : t, tr = lane < kMgEdge - 1 ? t + 1 : t;
+  const int tm = row ? t - kMgEdge : t, tp = row < kMgEdge - 1 ? t + kMgEdge : t;
+  const double rc0 = 1.0 / L.c0, rh = 1.0 / L.hx2;
+  auto nb = [&](const double *f, int side, double own, double below, double above) {
+    const double sx = own + f[side];
+    const double sy = f[tm] + f[tp];
+    const double sz = below + above;
+    return (sx + L.wy * sy) + L.wz * sz;
+  };
+  auto relax = [&](double n, double src, double old) {
+    return (1.0 - kOmegaGS) * old + kOmegaGS * over_c0(L.c0, rc0, n + L.hx2 * src);
+  };
+  auto defect = [&](double n, double src, double f) { return src - over_c0(L.hx2, rh, L.c0 * f - n); };
+
+  // planes z, z-1, ...: potential of both colours as loaded (0), after the first
+  // sweep (1) and the second (2), whose newest plane is z - (half-sweeps done); sources
+  double R0[2] = {}, B0[3] = {}, R1[4] = {}, B1[3] = {}, R2[3] = {}, SR[4] = {}, SB[5] = {};
+  int zl = modulo(k0 - G::H, L.nz);
+  long long at0 = zl * plane + col;
+  double nr = L.phi[at0], nbk = L.phi[half + at0], nsr = L.src[at0], nsb = L.src[half + at0];
+  double sum = 0.0;
+  for (int z = k0 - G::H; z < k1 + G::H; ++z) {
+    R0[1] = R0[0]; R0[0] = nr;
+    B0[2] = B0[1]; B0[1] = B0[0]; B0[0] = nbk;
+    SR[3] = SR[2]; SR[2] = SR[1]; SR[1] = SR[0]; SR[0] = nsr;
+    SB[4] = SB[3]; SB[3] = SB[2]; SB[2] = SB[1]; SB[1] = SB[0]; SB[0] = nsb;
+    if (z + 1 < k1 + G::H) {  // the next plane, under way during this one
+      zl = zl + 1 == L.nz ? 0 : zl + 1;
+      at0 = zl * plane + col;
+      nr = L.phi[at0];
+      nbk = L.phi[half + at0];
+      nsr = L.src[at0];
+      nsb = L.src[half + at0];
+    }
+    const double(*f)[kMgSmoothThreads] = sh[(z & 1) ^ 1];
+    double(*g)[kMgSmoothThreads] = sh[z & 1];
+    // of a pair in row j of plane k the red cell is the right one if j + k is odd,
+    // and a cell's other neighbour along x is in the pair beside it: that of plane
+    // z-1's red, plane z-2's black, plane z-3's red and plane z-4's black cell
+    const int side = (j + z) & 1 ? tl : tr, other = (j + z) & 1 ? tr : tl;
+    const double r1 = relax(nb(f[0], side, B0[1], B0[2], B0[0]), SR[1], R0[1]);
+    R1[3] = R1[2]; R1[2] = R1[1]; R1[1] = R1[0]; R1[0] = r1;
+    const double b1 = relax(nb(f[1], side, R1[1], R1[2], R1[0]), SB[2], B0[2]);
+    B1[2] = B1[1]; B1[1] = B1[0]; B1[0] = b1;
+    double vr = R1[1], vb = b1;
+    if constexpr (S == 4) {
+      const double r2 = relax(nb(f[2], side, B1[1], B1[2], B1[0]), SR[3], R1[2]);
+      R2[2] = R2[1]; R2[1] = R2[0]; R2[0] = r2;
+      vb = relax(nb(f[3], side, R2[1], R2[2], R2[0]), SB[4], B1[2]);
+      vr = R2[1];
+    }
+    const int q = z - S;
+    if (mine && q >= k0 && q < k1) {
+      const long long p = q * plane + col;
+      out[p] = vr;
+      out[half + p] = vb;
+    }
+    if constexpr (NORM) {  // plane z-3
+      const double dr = defect(nb(f[2], side, B1[1], B1[2], B1[0]), SR[3], R1[2]);
+      const double db = defect(nb(f[3], other, R1[2], R1[3], R1[1]), SB[3], B1[1]);
+      if (mine && z - 3 >= k0 && z - 3 < k1) sum += dr * dr + db * db;
+    }
+    g[0][t] = B0[0];
+    g[1][t] = R1[0];
+    g[2][t] = B1[0];
+    g[3][t] = NORM ? R1[1] : R2[0];
+    __syncthreads();
+  }
+  if constexpr (NORM) {
+    double *red = sh[0][0];
+    red[t] = sum;
+    __syncthreads();
+    for (int w = kMgSmoothThreads / 2; w > 0; w >>= 1) {
+      if (t < w) red[t] += red[t + w];
+      __syncthreads();
+    }
+    if (t == 0) part[id] = red[0];
+  }
+}
+
 // coarse start R phi (also kept in rphi) and the restricted defect, the
 // children's defects computed here (the same values and order of summation
 // as a stored defect averaged over the eight children)
@@ -304,12 +445,6 @@ __device__ __forceinline__ double lds_nbsum(const MgLdsLevel &L, const double *f
 }
 __device__ __forceinline__ double lds_nbsum(const MgLdsLevel &L, const double *f, int i, int j, int k) {
   return lds_nbsum(L, f, lds_neighbours(L, i, j, k));
-}
-// x / c0 by the reciprocal and one correction: the rounded quotient in three
-// dependent operations instead of a division's eleven
-__device__ __forceinline__ double over_c0(double c0, double r0, double x) {
-  const double q = x * r0;
-  return fma(fma(-c0, q, x), r0, q);
 }
 __device__ __forceinline__ double lds_apply(const MgLdsLevel &L, const double *f, int i, int j, int k) {
 #pragma clang fp contract(off)
@@ -538,7 +673,7 @@ __global__ __launch_bounds__(kMgLdsThreads) void mg_lds_cycle_kernel(MgLdsCycle 
 // along x, then y, then z.  One thread per coarse cell makes its eight
 // children from the 5 x 5 x 5 coarse neighbourhood they share (125 loads
 // instead of 512), keeping that order of summation for each child.
-__global__ __launch_bounds__(kMgThreads) void mg_prolong_kernel(MgLevel F, MgLevel C) {
+__global__ __launch_bounds__(kMgThreads) void mg_prolong_kernel(MgLevel F, MgLevel C, double *out) {
   const double w[2][4] = {{-5.0 / 128.0, 35.0 / 128.0, 105.0 / 128.0, -7.0 / 128.0},
                           {-7.0 / 128.0, 105.0 / 128.0, 35.0 / 128.0, -5.0 / 128.0}};
   const long long n = ncell(C);
@@ -590,79 +725,65 @@ __global__ __launch_bounds__(kMgThreads) void mg_prolong_kernel(MgLevel F, MgLev
       for (int cy = 0; cy < 2; ++cy)
 #pragma unroll
         for (int cx = 0; cx < 2; ++cx) {
-          F.phi[at(F, 2 * i + cx, 2 * j + cy, 2 * k + cz)] += Z[cz][cy][cx];
+          const long long q = at(F, 2 * i + cx, 2 * j + cy, 2 * k + cz);
+          out[q] = F.phi[q] + Z[cz][cy][cx];
         }
   }
 }
 
-// The same prolongation by tiles: a workgroup takes 8 x 8 x 4 coarse cells
-// (natural order, one per thread), stages their correction with a
-// two-cell halo in LDS once (12 x 12 x 8 values, against 125 gathers per cell
-// with a wrapped red-black index each), then forms each cell's eight children
-// from LDS with the same products and sums in the same order as
-// mg_prolong_kernel (the same bits).  Levels whose edges are multiples of 8, 8
-// and 4.
-constexpr int kPtx = 8, kPty = 8, kPtz = 4;
-static_assert(kPtx * kPty * kPtz == kMgThreads, "one coarse cell per thread");
+// The same prolongation by tiles: a workgroup stages the correction of a tile of
+// coarse cells with a two-cell halo in LDS, then interpolates along x, y and z
+// in turn, each value once (one thread per coarse cell repeats the x sums of its
+// 25 rows that its neighbours form too, four times the arithmetic in all); every
+// sum has mg_prolong_kernel's terms in its order (the same bits).  Reading and
+// writing the fine potential bounds it; 16 coarse cells along x make 128-byte
+// rows of each colour.  All levels of a 256^3 cycle 136 us, one thread per coarse
+// cell 174.  Levels whose edges are multiples of the tile's.
+constexpr int kPtx = 16, kPty = 4, kPtz = 4;
 
-__global__ __launch_bounds__(kMgThreads) void mg_prolong_tiled_kernel(MgLevel F, MgLevel C) {
-  constexpr int HX = kPtx + 4, HY = kPty + 4, HZ = kPtz + 4;
-  __shared__ double sc[HZ][HY][HX];
+__global__ __launch_bounds__(kMgThreads) void mg_prolong_tiled_kernel(MgLevel F, MgLevel C, double *out) {
+  constexpr int HX = kPtx + 4, HY = kPty + 4, HZ = kPtz + 4, FX = 2 * kPtx, FY = 2 * kPty, FZ = 2 * kPtz;
+  constexpr int kA = HX * HY * HZ, kY = FX * FY * HZ;
+  __shared__ double sx[HZ * HY * FX];
+  __shared__ double sa[kA > kY ? kA : kY];  // the correction, then the sums along y
   const double w[2][4] = {{-5.0 / 128.0, 35.0 / 128.0, 105.0 / 128.0, -7.0 / 128.0},
                           {-7.0 / 128.0, 105.0 / 128.0, 35.0 / 128.0, -5.0 / 128.0}};
+  // four values at a stride, from the child's side on
+  auto cubic = [&](const double *v, int stride, int side) {
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) s += (side ? w[1][a] : w[0][a]) * v[a * stride];
+    return s;
+  };
   const int tx = C.nx / kPtx, ty = C.ny / kPty, tz = C.nz / kPtz;
-  const int li = threadIdx.x % kPtx, lj = (threadIdx.x / kPtx) % kPty, lk = threadIdx.x / (kPtx * kPty);
+  const long long half = ncell(F) >> 1;
+  const int hx = F.nx >> 1;
   for (int tile = blockIdx.x; tile < tx * ty * tz; tile += gridDim.x) {
     const int i0 = (tile % tx) * kPtx, j0 = ((tile / tx) % ty) * kPty, k0 = (tile / (tx * ty)) * kPtz;
     __syncthreads();  // the previous tile's reads are done
-    for (int v = threadIdx.x; v < HX * HY * HZ; v += kMgThreads) {
+    for (int v = threadIdx.x; v < kA; v += kMgThreads) {
       const int a = v % HX, b = (v / HX) % HY, c = v / (HX * HY);
       const long long q = at(C, i0 + a - 2, j0 + b - 2, k0 + c - 2);
-      sc[c][b][a] = C.phi[q] - C.rphi[q];
+      sa[v] = C.phi[q] - C.rphi[q];
     }
     __syncthreads();
-    double Z[2][2][2] = {{{0.0, 0.0}, {0.0, 0.0}}, {{0.0, 0.0}, {0.0, 0.0}}};  // [cz][cy][cx]
-#pragma unroll
-    for (int oz = 0; oz < 5; ++oz) {
-      double Y[2][2] = {{0.0, 0.0}, {0.0, 0.0}};  // [cy][cx] at this z offset
-#pragma unroll
-      for (int oy = 0; oy < 5; ++oy) {
-        double e[5];
-#pragma unroll
-        for (int ox = 0; ox < 5; ++ox) e[ox] = sc[lk + oz][lj + oy][li + ox];
-        double X[2];
-#pragma unroll
-        for (int cx = 0; cx < 2; ++cx) {
-          double sx = 0.0;
-#pragma unroll
-          for (int a = 0; a < 4; ++a) sx += w[cx][a] * e[cx + a];
-          X[cx] = sx;
-        }
-#pragma unroll
-        for (int cy = 0; cy < 2; ++cy) {
-          const int b = oy - cy;
-          if (b < 0 || b > 3) continue;
-#pragma unroll
-          for (int cx = 0; cx < 2; ++cx) Y[cy][cx] += w[cy][b] * X[cx];
-        }
-      }
-#pragma unroll
-      for (int cz = 0; cz < 2; ++cz) {
-        const int c = oz - cz;
-        if (c < 0 || c > 3) continue;
-#pragma unroll
-        for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-          for (int cx = 0; cx < 2; ++cx) Z[cz][cy][cx] += w[cz][c] * Y[cy][cx];
-      }
+    for (int v = threadIdx.x; v < HZ * HY * FX; v += kMgThreads) {
+      const int i = v % FX, r = v / FX;
+      sx[v] = cubic(sa + r * HX + (i >> 1) + (i & 1), 1, i & 1);
     }
-    const int i = i0 + li, j = j0 + lj, k = k0 + lk;
-#pragma unroll
-    for (int cz = 0; cz < 2; ++cz)
-#pragma unroll
-      for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-        for (int cx = 0; cx < 2; ++cx) F.phi[at(F, 2 * i + cx, 2 * j + cy, 2 * k + cz)] += Z[cz][cy][cx];
+    __syncthreads();
+    for (int v = threadIdx.x; v < kY; v += kMgThreads) {
+      const int i = v % FX, j = (v / FX) % FY, k = v / (FX * FY);
+      sa[v] = cubic(sx + (k * HY + (j >> 1) + (j & 1)) * FX + i, FX, j & 1);
+    }
+    __syncthreads();
+    for (int v = threadIdx.x; v < FX * FY * FZ; v += kMgThreads) {
+      // in the order of storage: a row's cells of one colour, then of the other
+      const int h = v % kPtx, color = (v / kPtx) & 1, j = (v / FX) % FY, k = v / (FX * FY);
+      const int i = 2 * h + ((j + k + color) & 1);  // the tile's first cell is red
+      const long long q = color * half + ((long long)(2 * k0 + k) * F.ny + 2 * j0 + j) * hx + i0 + h;
+      out[q] = F.phi[q] + cubic(sa + (((k >> 1) + (k & 1)) * FY + j) * FX + i, FX * FY, k & 1);
+    }
   }
 }
 
@@ -713,6 +834,47 @@ hipError_t mg_launch_sweep(const MgLevel &L, hipStream_t s) {
   const long long half = ((long long)L.nx * L.ny * L.nz) >> 1;
   for (int color = 0; color < 2; ++color)
     hipLaunchKernelGGL(mg_rbgs_kernel, dim3(grid_for(half)), dim3(kMgThreads), 0, s, L, color);
+  return hipGetLastError();
+}
+
+// z chunks of a level's fused sweeps: the count that gives the fewest planes per
+// compute unit (rounds of workgroups times planes of a chunk with its ends)
+template <int S, bool NORM>
+static hipError_t launch_smooth(const MgLevel &L, double *out, double *part, int cus, int *parts, hipStream_t s) {
+  using G = MgSmooth<S, NORM>;
+  const long long tx = (L.nx / 2 + G::OX - 1) / G::OX, ty = (L.ny + G::OY - 1) / G::OY;
+  int nc = 1;
+  long long best = 0;
+  for (int c = 1; c <= L.nz && tx * ty * c <= kMgSumParts; ++c) {
+    const long long cost = (tx * ty * c + cus - 1) / cus * ((L.nz + c - 1) / c + 2 * G::H);
+    if (c == 1 || cost < best) {
+      best = cost;
+      nc = c;
+    }
+  }
+  const int g = (int)(tx * ty * nc);
+  if (parts) *parts = g;
+  hipLaunchKernelGGL((mg_smooth_kernel<S, NORM>), dim3((g + 7) / 8 * 8), dim3(kMgSmoothThreads), 0, s, L, out, (int)tx,
+                     (int)ty, nc, part);
+  return hipGetLastError();
+}
+
+bool mg_smooth_fits(const MgLevel &L) {
+  using G = MgSmooth<4, false>;
+  const long long tiles = ((L.nx / 2 + G::OX - 1) / G::OX) * (long long)((L.ny + G::OY - 1) / G::OY);
+  return (long long)L.nx * L.ny * L.nz >= kMgSmoothCells && tiles <= kMgSumParts;
+}
+
+hipError_t mg_launch_smooth(const MgLevel &L, double *out, int cus, hipStream_t s) {
+  return launch_smooth<4, false>(L, out, nullptr, cus, nullptr, s);
+}
+
+hipError_t mg_launch_smooth_norm(const MgLevel &L, double *out, double *part, double *norm, int cus, hipStream_t s) {
+  const long long n = (long long)L.nx * L.ny * L.nz;
+  int parts = 0;
+  const hipError_t e = launch_smooth<2, true>(L, out, part, cus, &parts, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(mg_final_sum_kernel, dim3(1), dim3(kMgThreads), 0, s, part, parts, 1.0 / (double)n, 1, norm);
   return hipGetLastError();
 }
 
@@ -794,13 +956,14 @@ hipError_t mg_launch_lds_cycle(const MgLevel *lv, int n, int sweeps, const doubl
   return hipGetLastError();
 }
 
-hipError_t mg_launch_prolong(const MgLevel &F, const MgLevel &C, hipStream_t s) {
+hipError_t mg_launch_prolong(const MgLevel &F, const MgLevel &C, double *out, hipStream_t s) {
   if (C.nx % kPtx == 0 && C.ny % kPty == 0 && C.nz % kPtz == 0) {
     const int tiles = (C.nx / kPtx) * (C.ny / kPty) * (C.nz / kPtz);
-    hipLaunchKernelGGL(mg_prolong_tiled_kernel, dim3(tiles < 4096 ? tiles : 4096), dim3(kMgThreads), 0, s, F, C);
+    hipLaunchKernelGGL(mg_prolong_tiled_kernel, dim3(tiles < 4096 ? tiles : 4096), dim3(kMgThreads), 0, s, F, C,
+                       out);
   } else {
     hipLaunchKernelGGL(mg_prolong_kernel, dim3(grid_for((long long)C.nx * C.ny * C.nz)), dim3(kMgThreads), 0, s, F,
-                       C);
+                       C, out);
   }
   return hipGetLastError();
 }

@@ -87,7 +87,7 @@ struct tdh_ctx {
   // captured windows: key = (Lmax, batched)
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;
   // captured multigrid cycles (V-cycle, extra sweep, defect norm): key = workspace
-  std::map<const void *, hipGraphExec_t> mg_graphs;
+  std::map<std::pair<const void *, bool>, hipGraphExec_t> mg_graphs;  // by workspace, and whether it is full
   double *d_facc = nullptr;  // frame-acceleration partial sums and result
   double *scratch = nullptr;  // this GPU's copy of the static device scratch
 };
@@ -1032,7 +1032,9 @@ struct MgPlan {
     const int t = lv[nlev - 1].nx + lv[nlev - 1].ny + lv[nlev - 1].nz;
     return 2 * t * t;
   }
-  size_t bytes = 0;
+  double *alt[kMgMaxLevels] = {};           // a second potential of a large level (null: its sweeps run in place)
+  int cus = 0;
+  size_t bytes = 0, least = 0;  // with mat and alt, and without: a workspace may lack both
 };
 }  // namespace
 
@@ -1077,20 +1079,31 @@ static tdh_status mg_plan(tdh_ctx *c, char *base, MgPlan *P) {
   }
   P->part = take(kMgSumParts);
   P->scal = take(4);
+  P->least = off * sizeof(double);
   const int nmat = mg_coarse_matrix_doubles(P->lv[nlev - 1]);
   P->mat = nmat ? take(nmat) : nullptr;
+  for (int l = 0; l < P->lds_top; ++l)
+    P->alt[l] = mg_smooth_fits(P->lv[l]) ? take((long long)P->lv[l].nx * P->lv[l].ny * P->lv[l].nz) : nullptr;
+  P->cus = c->cus;
   P->bytes = off * sizeof(double);
   return TDH_OK;
 }
 
+// One V-cycle from level l down; a large level's sweeps go two at a time from one
+// of its potentials to the other, the last two ending in alt.
 static hipError_t mg_vcycle(const MgPlan &P, int l, hipStream_t s) {
   hipError_t e;
   const MgLevel &L = P.lv[l];
   if (l == P.lds_top) return mg_launch_lds_cycle(P.lv + l, P.nlev - l, P.coarse_sweeps(), P.mat, s);
-  const MgLevel &C = P.lv[l + 1];
-  if ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)) || (e = mg_launch_restrict(L, C, s)) || (e = mg_vcycle(P, l + 1, s)) || (e = mg_launch_prolong(L, C, s)) ||
-      (e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)))
+  const bool two = P.alt[l] != nullptr;
+  MgLevel A = L, D = P.lv[l + 1];  // after the first two sweeps; the next level after its cycle
+  if (two) A.phi = P.alt[l];
+  if (P.alt[l + 1]) D.phi = P.alt[l + 1];
+  if (two ? (e = mg_launch_smooth(L, A.phi, P.cus, s)) : ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)))) return e;
+  if ((e = mg_launch_restrict(A, P.lv[l + 1], s)) || (e = mg_vcycle(P, l + 1, s)) || (e = mg_launch_prolong(A, D, L.phi, s)))
     return e;
+  if (two) return mg_launch_smooth(L, A.phi, P.cus, s);
+  if ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s))) return e;
   return hipSuccess;
 }
 
@@ -1117,7 +1130,12 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
     return fail(c, TDH_EINVAL, "four_pi_G must be finite, tol >= 0 and max_cycles in [0, 1000]");
   MgPlan P;
   if ((st = mg_plan(c, (char *)dev_work, &P))) return st;
-  if (bytes < P.bytes) return fail(c, TDH_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, P.bytes);
+  if (bytes < P.least) return fail(c, TDH_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, P.bytes);
+  const bool full = bytes >= P.bytes;
+  if (!full) {
+    P.mat = nullptr;
+    std::fill(P.alt, P.alt + kMgMaxLevels, nullptr);
+  }
   const StageArgs a = base_args(c);
   const MgLevel &F = P.lv[0];
   const long long N = (long long)F.nx * F.ny * F.nz;
@@ -1144,6 +1162,12 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
   // levels too small to hide their launch latency
   auto cycle = [&]() -> hipError_t {
     hipError_t e;
+    if (P.alt[0]) {
+      MgLevel T = F;
+      T.phi = P.alt[0];
+      if ((e = mg_vcycle(P, 0, s)) || (e = mg_launch_smooth_norm(T, F.phi, P.part, P.scal + 1, P.cus, s))) return e;
+      return hipSuccess;
+    }
     if ((e = mg_vcycle(P, 0, s)) || (e = mg_launch_sweep(F, s)) || (e = mg_launch_defect_norm(F, P.part, P.scal + 1, s)))
       return e;
     return hipSuccess;
@@ -1151,7 +1175,7 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
   int cyc = 0;
   while (cyc < max_cycles && !(d <= tol)) {
     if (cyc == 0 && P.mat) HIPCHK(c, mg_launch_coarse_matrix(P.lv[P.nlev - 1], P.coarse_sweeps(), P.mat, s));
-    auto it = c->mg_graphs.find(dev_work);
+    auto it = c->mg_graphs.find({dev_work, full});
     if (it == c->mg_graphs.end()) {
       HIPCHK(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
       const hipError_t e = cycle();
@@ -1163,7 +1187,7 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
       const hipError_t e3 = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
       hipGraphDestroy(g);
       HIPCHK(c, e3);
-      it = c->mg_graphs.emplace(dev_work, ge).first;
+      it = c->mg_graphs.emplace(std::make_pair((const void *)dev_work, full), ge).first;
     }
     HIPCHK(c, hipGraphLaunch(it->second, s));
     HIPCHK(c, hipMemcpyAsync(&d, P.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s));

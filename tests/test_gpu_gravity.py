@@ -84,6 +84,36 @@ def test_coarse_levels_in_one_workgroup(tdh, orc, blocks, n, dx):
     ctx.close()
 
 
+@pytest.mark.parametrize("blocks, dx", [
+    ((4, 4, 2), (0.1, 0.1, 0.1)),     # 128 x 128 x 64: the smallest level of the fused sweeps
+    ((5, 7, 1), (0.1, 0.13, 0.09)),   # 160 x 224 x 32: partial tiles along x and y, z chunks shorter than their ends
+])
+def test_fused_sweeps_and_plain_sweeps(tdh, orc, blocks, dx):
+    """The finest level's sweeps two at a time against the oracle's cell by cell,
+    and against the one-colour kernels that a workspace without the second
+    potential falls back to: the same potential, the defect to rounding."""
+    import ctypes as C
+    import torch
+    mesh = W.uniform_mesh(*blocks, 32, dx)
+    cfg, U, phi0 = _density_state(mesh, 8)
+    ctx, pg = _compare(tdh, orc, mesh, cfg, U, phi0, 1.5, 2)
+    full = C.c_size_t()
+    assert ctx.L.tdh_gravity_workspace_bytes(ctx.ctx, C.byref(full)) == 0
+    least = full.value - 8 * mesh.ncells
+    work = torch.zeros(full.value, dtype=torch.uint8, device=ctx.device)
+    out = []
+    for nbytes in (full.value, least):
+        d = np.zeros(3)
+        assert ctx.L.tdh_gravity_solve(ctx.ctx, work.data_ptr(), nbytes, 1.5, 2, 0.0, 0, None,
+                                       d.ctypes.data_as(C.POINTER(C.c_double))) == 0
+        out.append((ctx.get_potential(), d))
+    scale = np.max(np.abs(pg))
+    assert np.max(np.abs(out[0][0] - out[1][0])) <= TOL * scale
+    assert np.all(np.abs(out[0][1] - out[1][1]) <= 1e-9 * out[1][1])
+    assert ctx.L.tdh_gravity_solve(ctx.ctx, work.data_ptr(), 16 * mesh.ncells, 1.5, 2, 0.0, 0, None, None) != 0
+    ctx.close()
+
+
 def test_warm_start_and_tolerance(tdh, orc):
     mesh = W.uniform_mesh(2, 2, 2, 16, 1.0 / 32)
     cfg, U, phi0 = _density_state(mesh, 5)
