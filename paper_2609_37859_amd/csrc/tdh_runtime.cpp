@@ -877,16 +877,14 @@ static tdh_status enqueue_subcycle(tdh_ctx *c, int k, bool batched) {
       }
     }
   }
-  HIPCHK(c, launch_commit(c->d_order, c->d_cnt_ge, lmin, c->d_par, c->stream));
+  HIPCHK(c, launch_commit(c->d_order, c->d_cnt_ge, lmin, c->d_par, c->nb, c->stream));
   c->stats.kernel_launches++;
   if (c->Lmax > 0 || c->amr) {  // coarse-fine faces are corrected on every coarse step
     const int fmax = 1 << c->Lmax;
     const int lc = (k + 1 == fmax) ? 0 : c->Lmax - ctz(k + 1);
     a.k = k + 1;
-    for (int d = 0; d < 3; ++d) {
-      HIPCHK(c, launch_reflux(a, lc, d, c->nmax, 1024, c->stream));
-      c->stats.kernel_launches++;
-    }
+    HIPCHK(c, launch_reflux(a, lc, c->nb, c->nmax, c->stream));
+    c->stats.kernel_launches++;
   }
   return TDH_OK;
 }
