@@ -343,13 +343,16 @@ static Phys make_phys(const tdh_config &g) {
 }
 
 // The second stage leaves the CFL minima of its output state on single-level
-// runs with the table EOS and no point mass: under LAT (also levels a caller
-// installs) the reflux after a sub-cycle still corrects blocks that have
-// completed, the ideal gas's separate reduction is cheaper than the stage's
-// extra work, and the point mass's term moves with time (the reduction takes
-// the host's time).
+// runs with the table EOS and no point mass, or with the ideal gas and no gravity
+// (linear ghosts: the compiled kinds): under LAT (also levels a caller installs)
+// the reflux after a sub-cycle still corrects blocks that have completed, in an
+// ideal gas's fixed potential the separate reduction is cheaper than the stage's
+// extra work, and the point mass's term moves with time (the reduction takes the
+// host's time).  16^3 ideal gas: a step with its reduction 47.9 -> 44.2 us.
 static bool stage_cfl(const tdh_ctx *c) {
-  return c->cfg.eos_kind == 1 && c->cfg.n_lat == 0 && c->Lmax == 0 && c->cfg.grav_kind != 2 && !c->amr;
+  if (c->cfg.n_lat != 0 || c->Lmax != 0 || c->amr) return false;
+  if (c->cfg.eos_kind == 1) return c->cfg.grav_kind != 2;
+  return c->cfg.grav_kind == 0 && !c->cfg.ghost_dense && c->nv == 5 + (c->cfg.dual ? 1 : 0);
 }
 
 static StageArgs base_args(tdh_ctx *c) {

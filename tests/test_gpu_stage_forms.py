@@ -104,3 +104,25 @@ def test_seeds_after_each_stage_are_the_states_cells(tdh, saha):
         # a target within rounding of a node may fall to either side
         assert np.mean(c != exact) < 1e-3 and np.max(np.abs(c - exact)) <= 1
         assert np.array_equal(c, cells[0])
+
+
+@pytest.mark.parametrize("dual", [0, 1])
+@pytest.mark.parametrize("riemann", [0, 1])
+@pytest.mark.parametrize("dense", [0, 1])
+def test_stage_minima_are_the_reductions(tdh, dual, riemann, dense):
+    """Ideal gas: the time step from the minima the last second stage left (where
+    it leaves any: not with dense ghosts, nor the split form) equals the one
+    reduced from the state, bit for bit."""
+    cfg = W.Config(dual=dual, riemann=riemann, ghost_dense=dense)
+    split = np.zeros((1, 2, 1), dtype=bool)
+    split[0, 1, 0] = True
+    mesh = W.mixed_mesh((1, 2, 1), 16, split, 0.03, bc=(1, 0, 1))
+    for tile in (0, tdh.tile_shapes().index(next(d for d in tdh.tile_shapes() if d[0] == 0))):
+        ctx = tdh.Context(cfg, mesh, W.random_smooth_state(mesh, cfg, 5, amp=0.3))
+        ctx.set_tile(tile)
+        for _ in range(2):
+            r = ctx.reduce_dt()
+            ctx.run_window(r[1] * 2 ** r[3], batched=True)
+        a, b = ctx.reduce_dt(), ctx.reduce_dt(static=True)
+        assert np.array_equal(a[0], b[0]) and a[1] == b[1]
+        ctx.close()
