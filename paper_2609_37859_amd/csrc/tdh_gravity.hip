@@ -198,7 +198,8 @@ __global__ __launch_bounds__(kMgThreads) void mg_defect_sq_partial_kernel(MgLeve
 
 // ---------------------------------------------------------------------------
 // Red-black sweeps of a large level in one pass over memory: S half-sweeps (two
-// or four) from L.phi to `out`, and with NORM the squared defect of the result.
+// or four) from L.phi to `out`, and then the squared defect of the result or the
+// coarse level's start (mg_restrict_kernel's values).
 // One colour's kernel reads and writes four half-arrays, so that two sweeps move
 // eight times the level's potential and the defect twice more; here they move
 // three (potential and source in, potential out) and the halo.  A workgroup
@@ -210,7 +211,8 @@ __global__ __launch_bounds__(kMgThreads) void mg_defect_sq_partial_kernel(MgLeve
 // of the 32 x 32 are written by two sweeps, 28 x 26 by one with the defect), and
 // one more plane at the ends of a z chunk.  The values are the one-colour
 // kernel's, the defect's sum is taken in another order.
-// 256^3: two sweeps 131 us against 250, a sweep and the defect 104 us against 258;
+// 256^3: two sweeps 131 us against 250 (with the restriction 156 against 365), a
+// sweep and the defect 104 us against 258;
 // registers held to 64 for two workgroups on a compute unit spill (twice as slow).
 // Levels of 2^20 cells and more: ten cycles of 256^3 12.7 -> 9.0 ms, 128^3 3.24 ->
 // 2.68, 128 x 128 x 64 2.50 -> 2.19; below, the tiles and z chunks are too few to
@@ -218,9 +220,10 @@ __global__ __launch_bounds__(kMgThreads) void mg_defect_sq_partial_kernel(MgLeve
 // ---------------------------------------------------------------------------
 constexpr int kMgSmoothThreads = 1024, kMgEdge = 32;
 constexpr long long kMgSmoothCells = 1 << 20;
-template <int S, bool NORM>
+enum { kMgPlain, kMgNorm, kMgRestrict };  // after the sweeps: nothing, the squared defect, the coarse level's start
+template <int S, int TAIL>
 struct MgSmooth {
-  static constexpr int H = S + (NORM ? 1 : 0);               // spoiled cells at every edge
+  static constexpr int H = S + (TAIL == kMgPlain ? 0 : 1);   // spoiled cells at every edge
   static constexpr int PX = (H + 1) / 2, PY = H;             // in pairs and rows
   static constexpr int OX = kMgEdge - 2 * PX, OY = kMgEdge - 2 * PY;
 };
@@ -230,18 +233,20 @@ __device__ __forceinline__ int modulo(int a, int n) {
   return a < 0 ? a + n : a;
 }
 
-template <int S, bool NORM>
+template <int S, int TAIL>
 __global__ __launch_bounds__(kMgSmoothThreads) void mg_smooth_kernel(MgLevel L, double *out, int tx, int ty, int nc,
-                                                                     double *part) {
+                                                                     double *part, MgLevel C) {
 #pragma clang fp contract(off)
-  using G = MgSmooth<S, NORM>;
-  static_assert((S == 2 || S == 4) && !(S == 4 && NORM), "the planes kept below");
-  __shared__ double sh[2][4][kMgSmoothThreads];
+  using G = MgSmooth<S, TAIL>;
+  static_assert(S == 2 ? TAIL != kMgRestrict : S == 4 && TAIL != kMgNorm, "the planes kept below");
+  constexpr bool NORM = TAIL == kMgNorm, REST = TAIL == kMgRestrict;
+  __shared__ double sh[2][REST ? 6 : 4][kMgSmoothThreads];
+  __shared__ double rows[REST ? 2 : 1][2][REST ? kMgSmoothThreads : 1];  // a plane's pair sums of potential and defect
   // workgroups of one XCD take consecutive tiles: neighbours share its L2
   const int per = gridDim.x / 8, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (id >= tx * ty * nc) return;
   const int ti = id % tx, tj = (id / tx) % ty, tc = id / (tx * ty);
-  const int k0 = (int)((long long)L.nz * tc / nc), k1 = (int)((long long)L.nz * (tc + 1) / nc);
+  const int k0 = 2 * (int)((long long)(L.nz / 2) * tc / nc), k1 = 2 * (int)((long long)(L.nz / 2) * (tc + 1) / nc);
   const int t = threadIdx.x, lane = t & (kMgEdge - 1), row = t / kMgEdge;
   const int hx = L.nx >> 1;
   const int pi = ti * G::OX + lane - G::PX, pj = tj * G::OY + row - G::PY;
@@ -267,16 +272,16 @@ __global__ __launch_bounds__(kMgSmoothThreads) void mg_smooth_kernel(MgLevel L, 
 
   // planes z, z-1, ...: potential of both colours as loaded (0), after the first
   // sweep (1) and the second (2), whose newest plane is z - (half-sweeps done); sources
-  double R0[2] = {}, B0[3] = {}, R1[4] = {}, B1[3] = {}, R2[3] = {}, SR[4] = {}, SB[5] = {};
+  double R0[2] = {}, B0[3] = {}, R1[4] = {}, B1[3] = {}, R2[4] = {}, B2[3] = {}, SR[6] = {}, SB[6] = {};
   int zl = modulo(k0 - G::H, L.nz);
   long long at0 = zl * plane + col;
   double nr = L.phi[at0], nbk = L.phi[half + at0], nsr = L.src[at0], nsb = L.src[half + at0];
-  double sum = 0.0;
-  for (int z = k0 - G::H; z < k1 + G::H; ++z) {
+  double sum = 0.0, f0 = 0.0, d0 = 0.0;
+  for (int z = k0 - G::H; z < k1 + G::H + (REST ? 1 : 0); ++z) {
     R0[1] = R0[0]; R0[0] = nr;
     B0[2] = B0[1]; B0[1] = B0[0]; B0[0] = nbk;
-    SR[3] = SR[2]; SR[2] = SR[1]; SR[1] = SR[0]; SR[0] = nsr;
-    SB[4] = SB[3]; SB[3] = SB[2]; SB[2] = SB[1]; SB[1] = SB[0]; SB[0] = nsb;
+    SR[5] = SR[4]; SR[4] = SR[3]; SR[3] = SR[2]; SR[2] = SR[1]; SR[1] = SR[0]; SR[0] = nsr;
+    SB[5] = SB[4]; SB[4] = SB[3]; SB[3] = SB[2]; SB[2] = SB[1]; SB[1] = SB[0]; SB[0] = nsb;
     if (z + 1 < k1 + G::H) {  // the next plane, under way during this one
       zl = zl + 1 == L.nz ? 0 : zl + 1;
       at0 = zl * plane + col;
@@ -298,9 +303,10 @@ __global__ __launch_bounds__(kMgSmoothThreads) void mg_smooth_kernel(MgLevel L, 
     double vr = R1[1], vb = b1;
     if constexpr (S == 4) {
       const double r2 = relax(nb(f[2], side, B1[1], B1[2], B1[0]), SR[3], R1[2]);
-      R2[2] = R2[1]; R2[1] = R2[0]; R2[0] = r2;
+      R2[3] = R2[2]; R2[2] = R2[1]; R2[1] = R2[0]; R2[0] = r2;
       vb = relax(nb(f[3], side, R2[1], R2[2], R2[0]), SB[4], B1[2]);
       vr = R2[1];
+      B2[2] = B2[1]; B2[1] = B2[0]; B2[0] = vb;
     }
     const int q = z - S;
     if (mine && q >= k0 && q < k1) {
@@ -312,6 +318,35 @@ __global__ __launch_bounds__(kMgSmoothThreads) void mg_smooth_kernel(MgLevel L, 
       const double dr = defect(nb(f[2], side, B1[1], B1[2], B1[0]), SR[3], R1[2]);
       const double db = defect(nb(f[3], other, R1[2], R1[3], R1[1]), SB[3], B1[1]);
       if (mine && z - 3 >= k0 && z - 3 < k1) sum += dr * dr + db * db;
+    }
+    if constexpr (REST) {
+      // plane z-6, whose rows' sums are in LDS: the children of one coarse cell
+      // are a pair in two rows and two planes
+      if (mine && (row & 1)) {
+        const double(*p)[kMgSmoothThreads] = rows[(z & 1) ^ 1];
+        const double fs = p[0][t] + p[0][t + kMgEdge], ds = p[1][t] + p[1][t + kMgEdge];
+        const int k = z - 6;
+        if (k & 1) {
+          if (k > k0 && k < k1) {
+            const int cj = pj >> 1, ck = k >> 1;
+            const long long q = ((pi + cj + ck) & 1) * (ncell(C) >> 1) + (((long long)ck * C.ny + cj) * C.nx + pi >> 1);
+            const double r = 0.125 * (f0 + fs);
+            C.phi[q] = r;
+            C.rphi[q] = r;
+            C.src[q] = 0.125 * (d0 + ds);
+          }
+        } else {
+          f0 = fs;
+          d0 = ds;
+        }
+      }
+      // plane z-5
+      const double dr = defect(nb(f[5], side, B2[1], B2[2], B2[0]), SR[5], R2[2]);
+      const double db = defect(nb(f[4], other, R2[2], R2[3], R2[1]), SB[5], B2[1]);
+      rows[z & 1][0][t] = R2[2] + B2[1];
+      rows[z & 1][1][t] = dr + db;
+      g[4][t] = R2[1];
+      g[5][t] = B2[0];
     }
     g[0][t] = B0[0];
     g[1][t] = R1[0];
@@ -839,14 +874,15 @@ hipError_t mg_launch_sweep(const MgLevel &L, hipStream_t s) {
 
 // z chunks of a level's fused sweeps: the count that gives the fewest planes per
 // compute unit (rounds of workgroups times planes of a chunk with its ends)
-template <int S, bool NORM>
-static hipError_t launch_smooth(const MgLevel &L, double *out, double *part, int cus, int *parts, hipStream_t s) {
-  using G = MgSmooth<S, NORM>;
+template <int S, int TAIL>
+static hipError_t launch_smooth(const MgLevel &L, double *out, double *part, const MgLevel &C, int cus, int *parts,
+                                hipStream_t s) {
+  using G = MgSmooth<S, TAIL>;
   const long long tx = (L.nx / 2 + G::OX - 1) / G::OX, ty = (L.ny + G::OY - 1) / G::OY;
   int nc = 1;
   long long best = 0;
-  for (int c = 1; c <= L.nz && tx * ty * c <= kMgSumParts; ++c) {
-    const long long cost = (tx * ty * c + cus - 1) / cus * ((L.nz + c - 1) / c + 2 * G::H);
+  for (int c = 1; c <= L.nz / 2 && tx * ty * c <= kMgSumParts; ++c) {
+    const long long cost = (tx * ty * c + cus - 1) / cus * (2 * ((L.nz / 2 + c - 1) / c) + 2 * G::H);
     if (c == 1 || cost < best) {
       best = cost;
       nc = c;
@@ -854,25 +890,44 @@ static hipError_t launch_smooth(const MgLevel &L, double *out, double *part, int
   }
   const int g = (int)(tx * ty * nc);
   if (parts) *parts = g;
-  hipLaunchKernelGGL((mg_smooth_kernel<S, NORM>), dim3((g + 7) / 8 * 8), dim3(kMgSmoothThreads), 0, s, L, out, (int)tx,
-                     (int)ty, nc, part);
+  hipLaunchKernelGGL((mg_smooth_kernel<S, TAIL>), dim3((g + 7) / 8 * 8), dim3(kMgSmoothThreads), 0, s, L, out, (int)tx,
+                     (int)ty, nc, part, C);
   return hipGetLastError();
 }
 
+// Two sweeps, then the restriction: with it from 2^22 cells on (ten cycles of 256^3
+// 8.95 -> 8.1 ms, 256 x 256 x 128 4.58 -> 4.40); on smaller levels the wider edge
+// costs more than the pass (128^3 2.68 -> 2.73, 128 x 128 x 64 2.19 -> 2.30).
+constexpr long long kMgRestrictCells = 1 << 22;
+
 bool mg_smooth_fits(const MgLevel &L) {
-  using G = MgSmooth<4, false>;
+  using G = MgSmooth<4, kMgRestrict>;
   const long long tiles = ((L.nx / 2 + G::OX - 1) / G::OX) * (long long)((L.ny + G::OY - 1) / G::OY);
   return (long long)L.nx * L.ny * L.nz >= kMgSmoothCells && tiles <= kMgSumParts;
 }
 
 hipError_t mg_launch_smooth(const MgLevel &L, double *out, int cus, hipStream_t s) {
-  return launch_smooth<4, false>(L, out, nullptr, cus, nullptr, s);
+  return launch_smooth<4, kMgPlain>(L, out, nullptr, L, cus, nullptr, s);
+}
+
+hipError_t mg_launch_smooth_restrict(const MgLevel &L, double *out, const MgLevel &C, int cus, hipStream_t s) {
+  if ((long long)L.nx * L.ny * L.nz < kMgRestrictCells) {
+    const hipError_t e = mg_launch_smooth(L, out, cus, s);
+    if (e != hipSuccess) return e;
+    MgLevel A = L;
+    A.phi = out;
+    return mg_launch_restrict(A, C, s);
+  }
+  const hipError_t e = launch_smooth<4, kMgRestrict>(L, out, nullptr, C, cus, nullptr, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(mg_coarse_source_kernel, dim3(grid_for((long long)C.nx * C.ny * C.nz)), dim3(kMgThreads), 0, s, C);
+  return hipGetLastError();
 }
 
 hipError_t mg_launch_smooth_norm(const MgLevel &L, double *out, double *part, double *norm, int cus, hipStream_t s) {
   const long long n = (long long)L.nx * L.ny * L.nz;
   int parts = 0;
-  const hipError_t e = launch_smooth<2, true>(L, out, part, cus, &parts, s);
+  const hipError_t e = launch_smooth<2, kMgNorm>(L, out, part, L, cus, &parts, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(mg_final_sum_kernel, dim3(1), dim3(kMgThreads), 0, s, part, parts, 1.0 / (double)n, 1, norm);
   return hipGetLastError();

@@ -148,9 +148,10 @@ hipError_t mg_launch_lds_cycle(const MgLevel *lv, int n, int sweeps, const doubl
 int mg_coarse_matrix_doubles(const MgLevel &C);
 hipError_t mg_launch_coarse_matrix(const MgLevel &C, int sweeps, double *mat, hipStream_t s);
 hipError_t mg_launch_prolong(const MgLevel &F, const MgLevel &C, double *out, hipStream_t s);  // out = F.phi + P e
-// large levels: two sweeps from L.phi to out; one sweep and the RMS defect of out
+// large levels: two sweeps from L.phi to out, also with mg_launch_restrict of the result; one sweep and the RMS defect of out
 bool mg_smooth_fits(const MgLevel &L);
 hipError_t mg_launch_smooth(const MgLevel &L, double *out, int cus, hipStream_t s);
+hipError_t mg_launch_smooth_restrict(const MgLevel &L, double *out, const MgLevel &C, int cus, hipStream_t s);
 hipError_t mg_launch_smooth_norm(const MgLevel &L, double *out, double *part, double *norm, int cus, hipStream_t s);
 hipError_t mg_launch_scatter(const MeshDev &m, int nblocks, int nmax, const MgLevel &F, double *phib, hipStream_t s);
 int mg_coarse_max();

@@ -1100,9 +1100,10 @@ static hipError_t mg_vcycle(const MgPlan &P, int l, hipStream_t s) {
   MgLevel A = L, D = P.lv[l + 1];  // after the first two sweeps; the next level after its cycle
   if (two) A.phi = P.alt[l];
   if (P.alt[l + 1]) D.phi = P.alt[l + 1];
-  if (two ? (e = mg_launch_smooth(L, A.phi, P.cus, s)) : ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)))) return e;
-  if ((e = mg_launch_restrict(A, P.lv[l + 1], s)) || (e = mg_vcycle(P, l + 1, s)) || (e = mg_launch_prolong(A, D, L.phi, s)))
+  if (two ? (e = mg_launch_smooth_restrict(L, A.phi, P.lv[l + 1], P.cus, s))
+          : ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s)) || (e = mg_launch_restrict(L, P.lv[l + 1], s))))
     return e;
+  if ((e = mg_vcycle(P, l + 1, s)) || (e = mg_launch_prolong(A, D, L.phi, s))) return e;
   if (two) return mg_launch_smooth(L, A.phi, P.cus, s);
   if ((e = mg_launch_sweep(L, s)) || (e = mg_launch_sweep(L, s))) return e;
   return hipSuccess;

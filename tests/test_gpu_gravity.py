@@ -86,6 +86,7 @@ def test_coarse_levels_in_one_workgroup(tdh, orc, blocks, n, dx):
 
 @pytest.mark.parametrize("blocks, dx", [
     ((4, 4, 2), (0.1, 0.1, 0.1)),     # 128 x 128 x 64: the smallest level of the fused sweeps
+    ((11, 12, 1), (0.1, 0.1, 0.1)),   # 352 x 384 x 32: the restriction too, partial tiles
     ((5, 7, 1), (0.1, 0.13, 0.09)),   # 160 x 224 x 32: partial tiles along x and y, z chunks shorter than their ends
 ])
 def test_fused_sweeps_and_plain_sweeps(tdh, orc, blocks, dx):
