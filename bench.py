@@ -13,11 +13,11 @@ delayed flux corrections and the level bookkeeping, inputs resident in HBM.
 
 Prints one JSON line.  `value` is the cell-updates/s of the learned form: all
 active levels in one launch per RK phase, the window replayed from a captured
-hipGraph, and before each stage but a window's first a pass that finds the
-table cell of every active cell's state by a search started from the learned
-network's prediction (the network is trained first on the GPU by the
-library's own kernels; training time reported, not timed).  Beside it: the
-plain form (one launch per level, bisection for every table query, no graph).
+hipGraph, every table search starting from the cell the last stage recorded
+for the state, or from the learned network's prediction where none is held
+(the network is trained first on the GPU by the library's own kernels;
+training time reported, not timed).  Beside it: the plain form (one launch per
+level, every table query searched from the table's own start cells, no graph).
 Both give the same bits.  Each form runs --warmup windows, then --repeats
 timed runs of exactly --steps windows; its rate is that of the median run,
 from the library's own update counters.  The roofline entry is the stage
@@ -77,18 +77,16 @@ def counters_from_profiles(workload, family="stage"):
 
 
 FORMS = {
-    "learned": "batched launches; before the second stage a pass finds the table cell of every cell's state by "
-               "a search started from the learned network's prediction; it seeds the cell's face and "
-               "compression queries (the first stage takes the cells the last second stage recorded)",
+    "learned": "batched launches; each stage records the table cells of its output states, which seed the next "
+               "stage's face and compression queries; where none are held the search starts from the learned "
+               "network's prediction",
     "learned_inkernel": "batched launches; each stage finds the table cells of its output states by searches "
                         "started from the learned network's prediction inside the stage kernel; they seed the "
                         "next stage's face and compression queries",
     "temporal": "batched launches; each stage finds the table cells of its output states by searches started "
                 "from its input states' cells; they seed the next stage's queries",
-    "chained": "batched launches; before the second stage the table cell of every cell's state is bisected; it "
-               "seeds the cell's face and compression queries (the first stage takes the cells the last second "
-               "stage recorded)",
-    "plain": "one launch per level; bisection for every table query",
+    "chained": "as learned, with searches from the table's own start cells where no cell is held",
+    "plain": "one launch per level; every table query searched from the table's own start cells",
     "learned_hlle": "the learned form with the HLLE Riemann solver of the paper's production runs",
 }
 
@@ -244,10 +242,10 @@ C5_WORKLOAD = ("production-shaped: 4096 MeshBlocks (1688 x 32^3 + 2408 x 16^3, 6
 
 C5_FORMS = {
     "learned": "LAT-batched (all active levels in one launch per RK phase, window replayed from a hipGraph); "
-               "before each stage but a window's first, a pass finds every active cell's table cell by a search "
-               "started from the learned network's prediction (the window's first stage takes the cells the CFL "
-               "reduction found); the cell seeds the cell's face and compression queries",
-    "plain": "one launch per level per RK phase, no graph; bisection for every table query",
+               "each stage and the CFL reduction record the table cells of their states, which seed the next "
+               "stage's face and compression queries; where none are held the search starts from the learned "
+               "network's prediction",
+    "plain": "one launch per level per RK phase, no graph; every table query searched from the table's start cells",
 }
 
 

@@ -81,7 +81,7 @@ typedef struct {
   double gm_bh, r_soft, r_exc; /* G M, softening length, excision radius (grav_kind 2) */
   double bh_x0[3], v_frame[3]; /* point-mass position at t = 0 and frame velocity */
   int inv_mode;   /* table inversion (every mode gives the same cell, hence the same result):
-                     0 bisection for every query;
+                     0 a search from the table's own start cells for every query;
                      1 each stage's face and compression queries start from the table
                        cell of the cell's stage-input state (a face state from its
                        own cell's) and step to their own; each stage records the
@@ -92,14 +92,15 @@ typedef struct {
                        query at hand;
                      2 as 3;
                      4 as 3 with the searches of cells for which none is held
-                       starting from the learned network's prediction (bisection
-                       while the network is off).
+                       starting from the learned network's prediction (the start
+                       cells while the network is off).
                      Where no cells are held (after a state upload) a pass before the
-                     first stage finds them: with the network in modes 1 and 4, by
-                     bisection in modes 2 and 3.  In modes 2 and 4 the CFL reduction
+                     first stage finds them: with the network in modes 1 and 4, from
+                     the start cells in modes 2 and 3.  In modes 2 and 4 the CFL reduction
                      (tdh_reduce_dt) records the cells of the state it reduces over
                      (its search for c_s finds them), and no pass is needed. */
-  int newton_max_iter; /* seeded secant steps before falling back to bisection (>= 0) */
+  int newton_max_iter; /* seeded secant steps before falling back to the search
+                          without a seed (>= 0) */
   int riemann;    /* 0 HLLC (Toro Sec. 10.4); 1 HLLE, the solver of the paper's production
                      runs (Table 1): the HLL flux with the same Davis wave-speed bounds */
   int ghost_dense; /* LAT ghosts of a neighbour that is mid-step at the stage time
@@ -313,8 +314,9 @@ tdh_status tdh_get_seed_cells(tdh_ctx *ctx, int32_t *host_cells);
 
 /* Batched EOS queries on device arrays of n values (n <= 2^31):
  *   invert: log10 rho, log10 e -> log10 T, table cell j, secant steps taken
- *           (-1 when the bisection fallback ran); mode as tdh_config.inv_mode
- *           with the seed taken from the network (mode 1) or bisection.
+ *           (-1 when the search without a seed, or the bisection
+ *           fallback, found it); mode as tdh_config.inv_mode with the seed
+ *           taken from the network (mode 1) or the search itself (mode 2).
  *   eval:   rho, U (internal energy density) -> P, c_s. */
 tdh_status tdh_eos_invert_batch(tdh_ctx *ctx, const double *dev_lrho, const double *dev_le, double *dev_lT,
                                 int32_t *dev_j, int32_t *dev_iters, int64_t n, int mode);
