@@ -68,6 +68,25 @@ def test_remap_matches_the_oracle(tdh, orc, case):
         assert np.array_equal(g, o)
 
 
+@pytest.mark.parametrize("ratio", [(0.3, 0.3, 0.3), (1.9, 1.9, 1.9), (2.0, 1.0, 0.7), (3.8, 3.8, 3.8), (4.0, 1.0, 1.0)])
+@pytest.mark.parametrize("n", [8, 16, 32])
+@pytest.mark.parametrize("dual", [0, 1])
+def test_remap_over_spacing_ratios(tdh, orc, ratio, n, dual):
+    """Target spacings of 0.3 to 4 source spacings (three taps per axis below
+    1.95, four from there, the cell-by-cell kernel from 3.9), on blocks of every
+    tile shape, shifted against the source and partly outside it."""
+    cfg = W.Config(dual=dual, rho_floor=1e-6, p_floor=1e-8)
+    src = W.mixed_mesh((2, 1, 2), 32, np.array([[[True, False]], [[False, True]]]), 1.0 / 32, bc=(0, 1, 1))
+    dx = np.array(ratio) / 32
+    dst = W.uniform_mesh(*[max(1, round(m / (n * r))) for m, r in zip((64, 32, 64), ratio)], n, tuple(dx),
+                         x0=(0.013, -0.021, 0.37 / 32), bc=(0, 1, 1))
+    U = _vortex_state(src, cfg)
+    g = _remap_gpu(tdh, cfg, src, U, dst)
+    err = rel_err(cfg.nv, dst, g, orc.remap(cfg, src, U, dst))
+    print(ratio, n, dual, "remap rel err", err)
+    assert np.all(err <= TOL)
+
+
 def test_galilean_boost_matches_the_oracle(tdh, orc):
     cfg = W.Config(dual=1)
     mesh = W.uniform_mesh(2, 2, 1, 16, 1.0 / 32)
