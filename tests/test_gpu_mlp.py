@@ -131,6 +131,29 @@ def test_adam_step_matches_oracle(gctx, orc):
             assert np.all(np.abs(pg - p0) > 0)      # every weight moved
 
 
+@pytest.mark.parametrize("batch", [64, 128, 4096, 65536])
+def test_training_steps_are_gradient_and_adam(gctx, batch):
+    """The training step's one kernel for sums, Adam and packing against the
+    gradient and the Adam step called one by one, from one part of 64 samples to
+    the most: the same sums in the same order, so the same weights bit for bit.
+    The samples are all alike, so that the batch drawn does not matter."""
+    import torch
+    x = torch.from_numpy(np.tile(np.array([[-3.0, 13.0]]), (batch, 1))).cuda()
+    lT = torch.full((batch,), 5.0, dtype=torch.float64, device="cuda")
+    p0 = W.mlp_init_params(seed=3)
+    gctx.mlp_init(p0, RANGES)
+    loss = gctx.mlp_train(x, lT, steps=3, batch=batch, lr=1e-3, seed=1)
+    trained = gctx.mlp_params()
+    gctx.mlp_init(p0, RANGES)
+    for k in range(3):
+        one, g = gctx.mlp_loss_grad(x, lT)
+        assert one == loss[k]
+        decayed = 0.5 * float(np.float32(1e-3)) * (1.0 + np.cos(np.pi * k / 3))  # training's cosine schedule
+        gctx.mlp_adam_step(g, float(np.float32(decayed)))
+    assert np.array_equal(trained, gctx.mlp_params())
+    assert not np.array_equal(trained, p0)
+
+
 def _train_seed(ctx, saha, steps=2000, n=1 << 20, seed=1):
     """C4 recipe: 2^20 table samples, log rho ~ U[-12, 2], log e uniform between
     the row's values at 1e3 K and 1e8 K; labels from the table inversion."""
