@@ -87,6 +87,29 @@ def test_remap_over_spacing_ratios(tdh, orc, ratio, n, dual):
     assert np.all(err <= TOL)
 
 
+@pytest.mark.parametrize("x0, bc", [
+    ((-40.3, -17.0, -33.9), (1, 1, 1)),   # the source in the middle of the target
+    ((0.2, 0.3, -60.0), (1, 1, 1)),       # from the target's low faces on
+    ((-130.0, 1.0, 2.0), (1, 1, 1)),      # no target cell inside the source
+    ((-50.0, 0.4, -50.0), (1, 0, 1)),     # periodic along y
+])
+@pytest.mark.parametrize("ratio", [0.9, 1.5, 1.9])
+@pytest.mark.parametrize("dual", [0, 1])
+def test_remap_onto_a_larger_domain(tdh, orc, x0, bc, ratio, dual):
+    """Targets most of whose cells lie beyond the source (x0: the target's corner
+    in source cells): the tiles cover only those inside, from the first whole
+    tile on, and the others are floor states."""
+    cfg = W.Config(dual=dual, rho_floor=1e-6, p_floor=1e-8)
+    src = W.uniform_mesh(2, 3, 2, 16, 1.0 / 32, bc=bc)
+    dst = W.uniform_mesh(3, 3, 3, 32, ratio / 32, x0=tuple(v / 32 for v in x0), bc=bc)
+    U = _vortex_state(src, cfg)
+    g = _remap_gpu(tdh, cfg, src, U, dst)
+    o = orc.remap(cfg, src, U, dst)
+    assert np.all(rel_err(cfg.nv, dst, g, o) <= TOL)
+    floor = W.to_global(dst, cfg.nv, o)[0] == cfg.rho_floor
+    assert np.array_equal(W.to_global(dst, cfg.nv, g)[0] == cfg.rho_floor, floor)
+
+
 def test_galilean_boost_matches_the_oracle(tdh, orc):
     cfg = W.Config(dual=1)
     mesh = W.uniform_mesh(2, 2, 1, 16, 1.0 / 32)
