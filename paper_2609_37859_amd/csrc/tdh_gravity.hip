@@ -587,34 +587,50 @@ __device__ __forceinline__ void lds_prolong(const MgLdsLevel &L, const MgLdsLeve
 
 // The coarsest level's sweeps: at most 2048 cells, so every thread owns at most
 // one cell of each colour, whose neighbour slots it finds once.  Up to 64 cells
-// of a colour one wave sweeps alone, without barriers.
-__device__ __forceinline__ void lds_coarse_solve(const MgLdsLevel &C, int sweeps, double *lds) {
+// of a colour one wave sweeps alone, without barriers (kMgOneWave); where some
+// waves have no cell (kMgSomeWaves) those only wait, since their idle passes
+// through LDS hold up the others': a cycle of 256 x 256 x 32 (512 coarsest
+// cells) takes 930 us, 1234 with every wave at work.  Where every wave has a cell
+// (kMgAllWaves) the check would only cost: 16 x 256 x 256 (2048 cells) 3.85 ms
+// per cycle, 4.61 with it.
+enum { kMgOneWave, kMgSomeWaves, kMgAllWaves };
+template <int WAVES>
+__device__ __forceinline__ void lds_coarse_sweeps(const MgLdsLevel &C, int sweeps, double *lds) {
 #pragma clang fp contract(off)
   double *phi = lds + C.phi;
   const int half = C.half;
-  const bool one_wave = half <= 64;
-  if (!one_wave || threadIdx.x < 64) {
-    const bool own = (int)threadIdx.x < half;
-    const int t = own ? (int)threadIdx.x : 0;
-    LdsNeighbours nb[2];
-    double hs[2], old[2];
+  const bool own = (int)threadIdx.x < half;
+  const bool busy = WAVES != kMgSomeWaves || 64 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < half;
+  const int t = own ? (int)threadIdx.x : 0;
+  LdsNeighbours nb[2];
+  double hs[2], old[2];
+#pragma unroll
+  for (int color = 0; color < 2; ++color) {
+    const LdsCell c = lds_cell(C, t, color);
+    nb[color] = lds_neighbours(C, c.i, c.j, c.k);
+    hs[color] = C.hx2 * lds[C.src + color * half + t];
+    old[color] = phi[color * half + t];
+  }
+  for (int s = 0; s < sweeps; ++s) {
 #pragma unroll
     for (int color = 0; color < 2; ++color) {
-      const LdsCell c = lds_cell(C, t, color);
-      nb[color] = lds_neighbours(C, c.i, c.j, c.k);
-      hs[color] = C.hx2 * lds[C.src + color * half + t];
-      old[color] = phi[color * half + t];
-    }
-    for (int s = 0; s < sweeps; ++s) {
-#pragma unroll
-      for (int color = 0; color < 2; ++color) {
+      if (busy) {
         const double gs = over_c0(C.c0, C.r0, lds_nbsum(C, phi, nb[color]) + hs[color]);
         old[color] = (1.0 - kOmegaGS) * old[color] + kOmegaGS * gs;
         if (own) phi[color * half + t] = old[color];
-        if (one_wave) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        else __syncthreads();
       }
+      if (WAVES == kMgOneWave) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      else __syncthreads();
     }
+  }
+}
+__device__ __forceinline__ void lds_coarse_solve(const MgLdsLevel &C, int sweeps, double *lds) {
+  if (C.half <= 64) {
+    if (threadIdx.x < 64) lds_coarse_sweeps<kMgOneWave>(C, sweeps, lds);
+  } else if (C.half <= kMgLdsThreads - 64) {
+    lds_coarse_sweeps<kMgSomeWaves>(C, sweeps, lds);
+  } else {
+    lds_coarse_sweeps<kMgAllWaves>(C, sweeps, lds);
   }
   __syncthreads();
 }

@@ -84,6 +84,20 @@ def test_coarse_levels_in_one_workgroup(tdh, orc, blocks, n, dx):
     ctx.close()
 
 
+@pytest.mark.parametrize("blocks", [
+    (17, 1, 1),    # 136 coarsest cells, 68 of a colour: the fewest that take a second wave
+    (6, 5, 1),     # 240
+    (8, 8, 1),     # 512: four waves of sixteen
+    (15, 16, 1),   # 1920, 960 of a colour: the most that leave a wave without a cell
+    (22, 11, 1),   # 1936, 968 of a colour: the last wave has eight
+])
+def test_swept_coarsest_level_by_waves(tdh, orc, blocks):
+    mesh = W.uniform_mesh(*blocks, 8, (0.1, 0.1, 0.1))
+    cfg, U, phi0 = _density_state(mesh, 7)
+    ctx, _ = _compare(tdh, orc, mesh, cfg, U, phi0, 1.5, 2)
+    ctx.close()
+
+
 @pytest.mark.parametrize("blocks, dx", [
     ((4, 4, 2), (0.1, 0.1, 0.1)),     # 128 x 128 x 64: the smallest level of the fused sweeps
     ((11, 12, 1), (0.1, 0.1, 0.1)),   # 352 x 384 x 32: the restriction too, partial tiles
