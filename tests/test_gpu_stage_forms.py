@@ -126,3 +126,25 @@ def test_stage_minima_are_the_reductions(tdh, dual, riemann, dense):
         a, b = ctx.reduce_dt(), ctx.reduce_dt(static=True)
         assert np.array_equal(a[0], b[0]) and a[1] == b[1]
         ctx.close()
+
+
+@pytest.mark.parametrize("var, dual", [(0, 0), (0, 1), (1, 1), (4, 1)])
+@pytest.mark.parametrize("riemann", [0, 1])
+@pytest.mark.parametrize("value", [1e160, 1e200, 1e290, np.inf, -np.inf, np.nan])
+def test_slopes_that_overflow_stay_infinite(tdh, orc, var, dual, riemann, value):
+    """The limiter's quotient where the product of the differences overflows, and
+    on infinities and NaN: a stage turns the same values NaN and infinite as the
+    oracle's 2 a b / (a + b) does, so a state that blows up is not hidden."""
+    cfg = W.Config(dual=dual, riemann=riemann)
+    mesh = W.uniform_mesh(1, 1, 1, 8, 0.1, bc=(1, 1, 1))
+    U = W.uniform_state(mesh, cfg)
+    q = W.unpack_block(mesh, cfg.nv, U, 0)
+    for k, f in ((3, 0.25), (4, 1.0), (5, 3.0)):  # a rising flank: equal signs either side of the middle cell
+        q[var, 4, 4, k] = f * value
+    ctx = tdh.Context(cfg, mesh, U)
+    ctx.step_level(0, 1e-4)
+    g = ctx.get_state()
+    ctx.close()
+    o, _ = orc.run_sync(cfg, mesh, U, 1, dts=[1e-4])
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(g), kind(o)), (kind.__name__, int(kind(g).sum()), int(kind(o).sum()))
