@@ -11,13 +11,17 @@ limit) and the window's 2^Lmax sub-cycles of RK2 stages (PLM, seeded table
 inversion, HLLC, divergence, gravity, dual-energy update, excision), the
 delayed flux corrections and the level bookkeeping, inputs resident in HBM.
 
-Prints one JSON line.  `value` is the cell-updates/s of the learned form: all
-active levels in one launch per RK phase, the window replayed from a captured
-hipGraph, every table search starting from the cell the last stage recorded
-for the state, or from the learned network's prediction where none is held
-(the network is trained first on the GPU by the library's own kernels;
-training time reported, not timed).  Beside it: the plain form (one launch per
-level, every table query searched from the table's own start cells, no graph).
+Prints one JSON line.  `value` is the cell-updates/s of the "learned" form
+(mode 4, the learned network on): all active levels in one launch per RK phase,
+the window replayed from a captured hipGraph, every table search starting from
+the cell the last stage or CFL reduction recorded for the state.  Mode 4 asks
+the network only where no cell is held; every timed window follows a reduction
+that left the cells, so the timed windows evaluate no network, and modes 2 and
+3 run the same kernels (the network inside the stage: c2's learned_inkernel; its
+batched queries: learned_seed).  The network is trained first on the GPU by the
+library's own kernels; training time reported, not timed.  Beside it: the plain
+form (one launch per level, every table query searched from the table's own
+start cells, no graph).
 Both give the same bits.  Each form runs --warmup windows, then --repeats
 timed runs of exactly --steps windows; its rate is that of the median run,
 from the library's own update counters.  The roofline entry is the stage
@@ -77,15 +81,15 @@ def counters_from_profiles(workload, family="stage"):
 
 
 FORMS = {
-    "learned": "batched launches; each stage records the table cells of its output states, which seed the next "
-               "stage's face and compression queries; where none are held the search starts from the learned "
-               "network's prediction",
+    "learned": "mode 4, batched launches; each stage and the first CFL reduction record the table cells of their "
+               "states, which seed the next stage's face and compression queries; the learned network is on and "
+               "would start searches where no cell is held, which no timed step meets (so it runs as temporal)",
     "learned_inkernel": "batched launches; each stage finds the table cells of its output states by searches "
                         "started from the learned network's prediction inside the stage kernel; they seed the "
                         "next stage's face and compression queries",
     "temporal": "batched launches; each stage finds the table cells of its output states by searches started "
                 "from its input states' cells; they seed the next stage's queries",
-    "chained": "as learned, with searches from the table's own start cells where no cell is held",
+    "chained": "mode 2: as learned, with searches from the table's own start cells where no cell is held",
     "plain": "one launch per level; every table query searched from the table's own start cells",
     "learned_hlle": "the learned form with the HLLE Riemann solver of the paper's production runs",
 }
@@ -242,9 +246,9 @@ C5_WORKLOAD = ("production-shaped: 4096 MeshBlocks (1688 x 32^3 + 2408 x 16^3, 6
 
 C5_FORMS = {
     "learned": "LAT-batched (all active levels in one launch per RK phase, window replayed from a hipGraph); "
-               "each stage and the CFL reduction record the table cells of their states, which seed the next "
-               "stage's face and compression queries; where none are held the search starts from the learned "
-               "network's prediction",
+               "mode 4: each stage and the CFL reduction record the table cells of their states, which seed the "
+               "next stage's face and compression queries; the learned network is on and would start searches "
+               "where no cell is held, which no timed window meets",
     "plain": "one launch per level per RK phase, no graph; every table query searched from the table's start cells",
 }
 

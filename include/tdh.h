@@ -94,11 +94,15 @@ typedef struct {
                      4 as 3 with the searches of cells for which none is held
                        starting from the learned network's prediction (the start
                        cells while the network is off).
-                     Where no cells are held (after a state upload) a pass before the
-                     first stage finds them: with the network in modes 1 and 4, from
-                     the start cells in modes 2 and 3.  In modes 2 and 4 the CFL reduction
-                     (tdh_reduce_dt) records the cells of the state it reduces over
-                     (its search for c_s finds them), and no pass is needed. */
+                     Where no cells are held (after a state upload, a remap, a boost or
+                     another table) a pass before the window's first stage finds
+                     them: with the network in modes 1 and 4, from the start cells in
+                     modes 2 and 3.  In modes 2 and 4 the CFL reduction
+                     (tdh_reduce_dt) records the cells of the state it reduces over:
+                     its search for c_s finds them, in mode 4 too from the start
+                     cells, and no pass is needed.  So in mode 4 the network runs for
+                     a window that no reduction of the same state precedes; once
+                     cells are held modes 2, 3 and 4 run alike. */
   int newton_max_iter; /* seeded secant steps before falling back to the search
                           without a seed (>= 0) */
   int riemann;    /* 0 HLLC (Toro Sec. 10.4); 1 HLLE, the solver of the paper's production
@@ -305,9 +309,9 @@ tdh_status tdh_frame_acceleration(tdh_ctx *ctx, double rho_min, double *host_A);
  * one ghost layer, blocks in order, x fastest.  Synchronises the stream. */
 tdh_status tdh_get_potential(tdh_ctx *ctx, double *host_phi);
 
-/* Seed table cells held for the current state (tdh_config.inv_mode 3; table
+/* Seed table cells held for the current state (tdh_config.inv_mode 1 to 4; table
  * EOS only): host_cells receives one int32 per cell, blocks in order, cells of
- * a block x fastest; -1 where none is held yet (after a state upload).  The
+ * a block x fastest; -1 where none is held yet (after a state upload, a remap or a boost, and in mode 0).  The
  * values only start searches; they never change a result.  Synchronises the
  * stream.  TDH_ESTATE without a table EOS or inside a window. */
 tdh_status tdh_get_seed_cells(tdh_ctx *ctx, int32_t *host_cells);

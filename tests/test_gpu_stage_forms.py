@@ -148,3 +148,36 @@ def test_slopes_that_overflow_stay_infinite(tdh, orc, var, dual, riemann, value)
     o, _ = orc.run_sync(cfg, mesh, U, 1, dts=[1e-4])
     for kind in (np.isnan, np.isposinf, np.isneginf):
         assert np.array_equal(kind(g), kind(o)), (kind.__name__, int(kind(g).sum()), int(kind(o).sum()))
+
+
+@pytest.mark.parametrize("name", ["levels", "refined"])
+def test_network_finds_the_cells_of_a_window_without_any(tdh, saha, name):
+    """Mode 4 with the network on, windows with levels on one and on two refinement
+    levels: a state set after its reduction holds no table cells, so the window
+    starts with the network's pass (one launch more than a window whose cells are
+    held), and gives mode 0's bits whatever the network predicts."""
+    box = (6, 8, 8, 10, 4, 6)
+    if name == "levels":
+        cfg, mesh, U = W.debris_stream_c5(saha, box=box)
+    else:
+        cfg, mesh, U = W.debris_stream_amr(saha, box=box)
+    out = {}
+    for mode, params in ((0, None), (4, 5), (4, 6)):
+        ctx = tdh.Context(cfg, mesh, U, table=saha, inv_mode=mode)
+        if params is not None:
+            ctx.mlp_init(W.mlp_init_params(params), W.seed_ranges(saha))
+            ctx.mlp_enable_seed(True)
+        _, dt0, _, lmax = ctx.reduce_dt()
+        assert lmax > 0
+        launches = []
+        for held in (False, True):
+            if not held:
+                ctx.set_state(U)
+            before = ctx.stats()["kernel_launches"]
+            ctx.run_window(dt0 * 2 ** lmax, batched=True)
+            launches.append(ctx.stats()["kernel_launches"] - before)
+            out.setdefault((mode, params), []).append(ctx.get_state())
+        assert launches[0] - launches[1] == (1 if mode == 4 else 0)
+        ctx.close()
+    for a, b in zip(out[4, 5] + out[4, 6], 2 * out[0, None]):
+        assert np.array_equal(a, b)
