@@ -90,3 +90,21 @@ def test_eval_batch_sizes(tdh, n):
     assert np.max(np.abs(P / (e * 10.0 ** 0.5) - 1.0)) < 1e-13
     assert np.max(np.abs(cs / np.sqrt(e * 10.0 ** -0.1) - 1.0)) < 1e-13
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [2 ** 19 - 1, 2 ** 19, 2 ** 19 + 257])
+def test_eval_either_side_of_two_queries_per_thread(tdh, n):
+    """The same bits from one query per thread and from two: the batch against
+    its pieces of less than half the size."""
+    import torch
+    t = _table("smooth")
+    mesh = W.uniform_mesh(1, 1, 1, 8, 1.0)
+    ctx = tdh.Context(W.Config(eos_kind=1), mesh, W.uniform_state(mesh, W.Config()), table=t)
+    rng = np.random.default_rng(n)
+    rho = torch.from_numpy(10.0 ** rng.uniform(-6.5, -2.0, n))
+    U = rho * torch.from_numpy(10.0 ** rng.uniform(11.5, 16.5, n))
+    whole = ctx.eos_eval(rho, U)
+    pieces = [ctx.eos_eval(r, u) for r, u in zip(rho.split(200001), U.split(200001))]
+    for k in range(2):
+        assert torch.equal(whole[k], torch.cat([p[k] for p in pieces]))
+    ctx.close()
