@@ -171,10 +171,11 @@ size_t tdh_table_bytes(int nrho, int nT);
  * log10 rho = lr0 + i*dlr, log10 T = lT0 + j*dlT; host arrays [nrho][nT],
  * T contiguous, of log10 P, log10 e (specific internal energy, strictly
  * increasing in T on every row) and log10 c_s^2.  2 <= nrho, nT <= 4096.
- * dev_table: caller-owned device buffer of at least tdh_table_bytes(nrho, nT)
+ * dev_table: caller-owned device buffer of tdh_table_bytes(nrho, nT)
  * bytes, 256-byte aligned, that the context reads until the next call of this
- * function or tdh_destroy (TDH_ENOMEM if smaller, TDH_EINVAL if null or
- * misaligned). */
+ * function or tdh_destroy (TDH_EINVAL if null or misaligned).  A buffer without
+ * room for the searches' start cells, the last 4 (nrho - 1) nT bytes rounded up
+ * to a multiple of 8, serves too, by slower searches; a smaller one is TDH_ENOMEM. */
 tdh_status tdh_set_eos_table(tdh_ctx *ctx, int nrho, int nT, double lr0, double dlr, double lT0, double dlT,
                              const double *host_logP, const double *host_loge, const double *host_logcs2,
                              void *dev_table, size_t table_bytes);

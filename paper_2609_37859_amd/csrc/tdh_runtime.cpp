@@ -587,17 +587,18 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   if (!lP || !le || !lc2) return fail(c, TDH_EINVAL, "null table array");
   if (!dev_table || ((uintptr_t)dev_table & 255))
     return fail(c, TDH_EINVAL, "table buffer must be non-null, 256-byte aligned");
-  if (table_bytes < tdh_table_bytes(nrho, nT))
-    return fail(c, TDH_ENOMEM, "table buffer holds %zu bytes, %zu needed", table_bytes, tdh_table_bytes(nrho, nT));
+  const TableLayout TL = table_layout(nrho, nT);
+  if (table_bytes < TL.guess_off * sizeof(double))
+    return fail(c, TDH_ENOMEM, "table buffer holds %zu bytes, %zu needed", table_bytes, TL.guess_off * sizeof(double));
+  const bool room = table_bytes >= TL.total * sizeof(double);  // for the start cells too
   if (!(dlr > 0.0) || !(dlT > 0.0)) return fail(c, TDH_EINVAL, "table spacings must be positive");
   for (int i = 0; i < nrho; ++i)
     for (int j = 0; j + 1 < nT; ++j)
       if (!(le[(size_t)i * nT + j + 1] > le[(size_t)i * nT + j]))
         return fail(c, TDH_EINVAL, "log e is not increasing in T on row %d", i);
   // pack by density-row pairs
-  const TableLayout TL = table_layout(nrho, nT);
   const size_t pc_off = TL.pc_off, rec_off = TL.rec_off, fn_off = TL.fn_off;
-  std::vector<double> packed(TL.total, 0.0);
+  std::vector<double> packed(room ? TL.total : TL.guess_off, 0.0);
   // log10 and 10^x tables, from the host's extended-precision library
   for (int i = 0; i < 128; ++i) {
     const double ci = 1.0 / (1.0 + (i + 0.5) / 128.0);
@@ -639,7 +640,7 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   const double dg = (hi - lo) / nbins;
   const bool binned = std::isfinite(dg) && dg > 0.0 && std::isfinite(1.0 / dg);  // else every search starts in bin 0
   unsigned short *guess = (unsigned short *)(packed.data() + TL.guess_off);
-  for (int i = 0; i + 1 < nrho; ++i) {
+  for (int i = 0; i + 1 < nrho && room; ++i) {
     const double *r0 = le + (size_t)i * nT, *r1 = r0 + nT;
     int j = 0;
     for (int b = 0; b < nbins && binned; ++b) {
@@ -664,7 +665,7 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   c->tab.rec = c->d_table + rec_off;
   c->tab.lg = (const double2 *)(c->d_table + fn_off);
   c->tab.ex = c->d_table + fn_off + 256;
-  c->tab.guess = (const unsigned short *)(c->d_table + TL.guess_off);
+  c->tab.guess = room ? (const unsigned short *)(c->d_table + TL.guess_off) : nullptr;
   c->tab.nbins = nbins;
   c->tab.g0 = binned ? lo : 0.0;
   c->tab.inv_dg = binned ? 1.0 / dg : 0.0;

@@ -108,3 +108,43 @@ def test_eval_either_side_of_two_queries_per_thread(tdh, n):
     for k in range(2):
         assert torch.equal(whole[k], torch.cat([p[k] for p in pieces]))
     ctx.close()
+
+
+def test_table_buffer_without_start_cells(tdh, saha):
+    """A buffer that holds the table but not the start cells: every search bisects,
+    with the same answers; a smaller one is refused."""
+    import ctypes as C
+    import torch
+    cfg = W.Config(eos_kind=1, dual=1, rho_floor=1e-12, p_floor=0.0, e_floor=saha.e_floor)
+    mesh = W.uniform_mesh(2, 1, 1, 8, 1e10)
+    rho = np.geomspace(1e-9, 1e-5, 8)
+
+    def fn(x, y, z):
+        r = rho[(np.floor(x / 1e10).astype(int)) % 8] + 0 * y + 0 * z
+        u = r * W.saha_pe(r, 2e4 + 0 * r)[1]
+        return [r, 0 * r, 0 * r, 0 * r, u, u]
+
+    U = W.pack_state(mesh, 6, fn)
+    x = torch.from_numpy(W.seed_training_samples(saha, 5001, 4))
+    lr, le = x[:, 0].contiguous(), x[:, 1].contiguous()
+    full = tdh.lib().tdh_table_bytes(saha.nrho, saha.nT)
+    least = full - (4 * (saha.nrho - 1) * saha.nT + 7) // 8 * 8
+    buf = torch.zeros(full, dtype=torch.uint8, device="cuda")
+    arrs = [np.ascontiguousarray(a) for a in (saha.lP, saha.le, saha.lc2)]
+    out = []
+    for nbytes in (full, least, least - 8):
+        ctx = tdh.Context(cfg, mesh, U, table=saha, inv_mode=3)
+        rc = ctx.L.tdh_set_eos_table(ctx.ctx, saha.nrho, saha.nT, saha.lr0, saha.dlr, saha.lT0, saha.dlT,
+                                     *(a.ctypes.data_as(C.POINTER(C.c_double)) for a in arrs), buf.data_ptr(), nbytes)
+        if nbytes < least:
+            assert rc == -2  # TDH_ENOMEM
+        else:
+            assert rc == 0
+            _, dt, _, _ = ctx.reduce_dt()
+            ctx.step_level(0, dt)
+            inv = ctx.eos_invert(lr, le, mode=0)
+            pc = ctx.eos_eval(10.0 ** lr, 10.0 ** (lr + le))
+            out.append([dt, ctx.get_state()] + [t.cpu().numpy() for t in inv + pc])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
