@@ -58,7 +58,8 @@ struct Table {
   const double *ex;
   // Start cells of a search without a seed: guess[i][b] is the cell of the
   // centre of bin b (of nbins over the table's range of log e) on the mean of
-  // density rows i and i+1; null where the table's buffer has no room for them.
+  // density rows i and i+1.  (Where the buffer has no room for them: the middle
+  // cell, for every bin, in the first record of each row pair.)
   const unsigned short *guess;
   int nbins;
   double g0, inv_dg;  // log e of the first bin's lower edge, bins per unit

@@ -638,17 +638,21 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   }
   const int nbins = kGuessBinsPerCell * nT;
   const double dg = (hi - lo) / nbins;
-  const bool binned = std::isfinite(dg) && dg > 0.0 && std::isfinite(1.0 / dg);  // else every search starts in bin 0
-  unsigned short *guess = (unsigned short *)(packed.data() + TL.guess_off);
-  for (int i = 0; i + 1 < nrho && room; ++i) {
+  const bool binned = room && std::isfinite(dg) && dg > 0.0 && std::isfinite(1.0 / dg);  // else every search starts in bin 0
+  for (int i = 0; i + 1 < nrho && binned; ++i) {
+    unsigned short *guess = (unsigned short *)(packed.data() + TL.guess_off) + (size_t)i * nbins;
     const double *r0 = le + (size_t)i * nT, *r1 = r0 + nT;
     int j = 0;
-    for (int b = 0; b < nbins && binned; ++b) {
+    for (int b = 0; b < nbins; ++b) {
       const double x = lo + (b + 0.5) * dg;
       while (j < nT - 2 && 0.5 * (r0[j + 1] + r1[j + 1]) <= x) ++j;
-      guess[(size_t)i * nbins + b] = (unsigned short)j;
+      guess[b] = (unsigned short)j;
     }
   }
+  // a buffer without room for them: every search starts from the middle cell, kept
+  // in the unused end of the record of each row pair's first cell
+  for (int i = 0; i + 1 < nrho && !room; ++i)
+    *(unsigned short *)(packed.data() + rec_off + 16 * (size_t)i * (nT - 1) + 12) = (unsigned short)((nT - 1) / 2);
   c->d_table = (double *)dev_table;
   HIPCHK(c, hipMemcpyAsync(c->d_table, packed.data(), packed.size() * sizeof(double), hipMemcpyHostToDevice,
                            c->stream));
@@ -665,10 +669,15 @@ extern "C" tdh_status tdh_set_eos_table(tdh_ctx *c, int nrho, int nT, double lr0
   c->tab.rec = c->d_table + rec_off;
   c->tab.lg = (const double2 *)(c->d_table + fn_off);
   c->tab.ex = c->d_table + fn_off + 256;
-  c->tab.guess = room ? (const unsigned short *)(c->d_table + TL.guess_off) : nullptr;
+  c->tab.guess = (const unsigned short *)(c->d_table + TL.guess_off);
   c->tab.nbins = nbins;
   c->tab.g0 = binned ? lo : 0.0;
   c->tab.inv_dg = binned ? 1.0 / dg : 0.0;
+  if (!room) {  // bin 0 of every row pair, in the record of its first cell
+    c->tab.guess = (const unsigned short *)(c->d_table + rec_off + 12);
+    c->tab.nbins = 64 * (nT - 1);  // 16-bit values in a row pair's records
+    c->tab.g0 = c->tab.inv_dg = 0.0;
+  }
   c->have_table = true;
   c->seeds_held = false;  // cells of another table
   c->cfl_parts = false;

@@ -111,8 +111,8 @@ def test_eval_either_side_of_two_queries_per_thread(tdh, n):
 
 
 def test_table_buffer_without_start_cells(tdh, saha):
-    """A buffer that holds the table but not the start cells: every search bisects,
-    with the same answers; a smaller one is refused."""
+    """A buffer that holds the table but not the start cells: every search starts in
+    the middle, with the same answers; a smaller one is refused."""
     import ctypes as C
     import torch
     cfg = W.Config(eos_kind=1, dual=1, rho_floor=1e-12, p_floor=0.0, e_floor=saha.e_floor)
