@@ -579,15 +579,22 @@ def seed_eval_section(T, W, table, params, windows=2):
 
 
 def mg_bytes_per_cycle(levels):
-    """Algorithmic HBM bytes of one multigrid cycle: per cell of every level but
-    the coarsest, four sweeps (read phi and the source, write phi: 24 B each),
-    the restriction of the solution and of the defect computed on the fly
-    (16 B read, 3 B written per fine cell), the coarse source and correction
-    passes (3 + 3 B per fine cell) and the prolongation (16 B read-modify-write,
-    1 B of coarse reads); on the finest level the extra sweep and the defect
-    norm (24 + 16 B)."""
+    """Algorithmic HBM bytes of one multigrid cycle, as the passes are launched.
+    Per cell of a level: two sweeps before and two after the coarser levels, two
+    per pass (24 B: potential and source read, potential written) on levels of
+    2^20 cells and more, one per pass below; the restriction (16 B read; none on
+    levels of 2^22 cells and more, where the sweeps form it) and its writes (3 B
+    per fine cell); the coarse source pass (3 B); the prolongation (16 B, and 2 B
+    of coarse reads).  The finest level's extra sweep, with the defect norm on the
+    way from 2^20 cells on (24 B, else 40).  The first level of at most 8192 cells
+    runs with the rest in one launch (24 B)."""
     n = [a * b * c for a, b, c in levels]
-    return 138 * sum(n[:-1]) + 40 * n[0]
+    total = 24 * n[0] if n[0] >= 1 << 20 else 40 * n[0]
+    for c in n[:-1]:
+        if c <= 8192:  # this level and the rest in one launch
+            return total + 24 * c
+        total += c * ((48 if c >= 1 << 20 else 96) + (0 if c >= 1 << 22 else 16) + 24)
+    return total
 
 
 def gravity_section(T, W, cycles, steps):
