@@ -1171,8 +1171,8 @@ extern "C" tdh_status tdh_gravity_solve(tdh_ctx *c, void *dev_work, size_t bytes
   HIPCHK(c, norm(&d));
   if (host_defects) host_defects[0] = d;
   // one cycle (V-cycle, the extra finest sweep, the defect norm) is captured
-  // once per workspace and replayed: about a hundred launches, most of them on
-  // levels too small to hide their launch latency
+  // once per workspace and replayed: 33 launches at 256^3, most of them on levels
+  // too small to hide their launch latency
   auto cycle = [&]() -> hipError_t {
     hipError_t e;
     if (P.alt[0]) {

@@ -181,3 +181,25 @@ def test_network_finds_the_cells_of_a_window_without_any(tdh, saha, name):
         ctx.close()
     for a, b in zip(out[4, 5] + out[4, 6], 2 * out[0, None]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("split", [0.75, 1.0])
+def test_flux_correction_on_many_blocks(tdh, orc, split):
+    """More blocks than a wave per 64 cells of every face would fill the chip with
+    (65536 waves): a wave takes several parts of a face of 32^2 cells, and blocks of
+    16^3 beside them take fewer.  Random levels, so that most faces are corrected."""
+    cfg = W.Config(n_lat=1)
+    rng = np.random.default_rng(12)
+    cut = rng.random((1, 10, 13)) < split
+    cut[0, 3, 4] = cut[0, 3, 5] = False
+    mesh = W.mixed_mesh((13, 10, 1), 32, cut, 1.0 / 64, bc=(1, 0, 1))
+    assert 6 * 16 * mesh.nblocks > 65536
+    U = W.random_smooth_state(mesh, cfg, 2, amp=0.3)
+    levels = rng.integers(0, 2, mesh.nblocks)
+    ctx = tdh.Context(cfg, mesh, U)
+    ctx.set_levels(levels)
+    ctx.run_window(2e-3, batched=True)
+    g = ctx.get_state()
+    ctx.close()
+    o, _ = orc.lat_window(cfg, mesh, U, levels, 1e-3)
+    assert np.all(rel_err(cfg.nv, mesh, g, o) <= TOL)
